@@ -8,7 +8,7 @@
 //    needs a single cross-lane exchange, the probabilities feed the
 //    O^T = V^T P^T product directly as its B operand, and the per-query
 //    rescale is a per-lane multiply.  Softmax runs in fp32 with exp2.
-//  * flash_attn_f32: the same result in plain fp32 (one thread per query).
+//  * flash_attn_f32: the same result in fp32 MFMA, keys split over a block's waves.
 //  * decode self / cross attention: one block per (row, head), streaming the
 //    row's cache once: scores for all keys, exact softmax, then the
 //    probability-weighted value sum.  The self variant first stores this
@@ -339,70 +339,186 @@ template void pack_attn_operand<bf16_t>(const float*, int, int, int, int, float,
                                         bf16_t*, hipStream_t);
 
 // ---------------------------------------------------------------------------
-// Encoder attention, fp32 (one thread per query, 32-key tiles in LDS)
+// Encoder attention, fp32, on v_mfma_f32_16x16x4_f32
+//
+// Bound by the fp32 matrix rate (4 * 1500^2 * 64 flops a head: 23 us for the
+// six heads of one clip at 148 TFLOP/s).  A block owns 16 NB queries of one
+// (clip, head); its 8 waves take the 16-key tiles in turn (tile t goes to
+// wave t % 8) and keep an online softmax of their own, merged through LDS at
+// the end, so one clip's few query blocks still put two waves on every SIMD
+// (one wave's exp2 and rescale run beside the other's MFMAs) and no barrier
+// sits in the key loop.
+//  * S^T = K Q^T: a lane's K operand is 16 bytes of one key's row and feeds
+//    four MFMAs, so K goes from the QKV buffer straight to registers.
+//  * In the MFMA output layout a lane holds one query's scores of keys
+//    4 (lane / 16) + r, which is the B operand of O^T += V^T P^T for MFMA r;
+//    the A operand is V[key][4 (lane % 16) + j] for dim component j: one
+//    coalesced 16-byte load of a key's row feeds the four j.
+//  * The query carries 1/sqrt(64) log2(e), so softmax works with exp2.
+// Nothing a query's result is made of depends on NB, which the launcher
+// picks so that the last round of blocks is not nearly empty.
+// One clip of 6 heads: 50 us a layer, 1146 us as one thread per query.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(128) void k_flash_f32(const float* __restrict__ qkv,
-                                                   float* __restrict__ out, int n_head) {
-  constexpr int KT = 32;
-  __shared__ float Ksh[KT][64];
-  __shared__ float Vsh[KT][64];
-  const int h = blockIdx.y, b = blockIdx.z;
+constexpr int FF_NW = 8;
+constexpr int FF_LD = 68;      // floats per merged query row in LDS (64 + pad)
+
+template <int NB>
+__global__ __launch_bounds__(FF_NW * 64) void k_flash_f32(const float* __restrict__ qkv,
+                                                          float* __restrict__ out, int n_head) {
+  constexpr int QT = 16 * NB, NT = (kCtx + 15) / 16;
+  extern __shared__ __attribute__((aligned(16))) float fsm[];
+  float* osh = fsm;                                // [FF_NW][QT][FF_LD]
+  float2* mlsh = (float2*)(fsm + FF_NW * QT * FF_LD);   // [FF_NW][QT] (max, sum)
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, g = lane >> 4;
+  const int h = blockIdx.y, b = blockIdx.z, q0 = blockIdx.x * QT;
   const int d = n_head * 64, ld3 = 3 * d;
-  const float* base = qkv + (int64_t)b * kCtx * ld3;
-  const int qrow = blockIdx.x * 128 + threadIdx.x;
-  const bool qvalid = qrow < kCtx;
-  float q[64], o[64];
-  const float* qp = base + (int64_t)(qvalid ? qrow : 0) * ld3 + h * 64;
+  const float* base = qkv + (int64_t)b * kCtx * ld3 + h * 64;
+
+  f32x4 qf[NB][4];
 #pragma unroll
-  for (int i = 0; i < 64; ++i) {
-    q[i] = qp[i] * 0.125f;
-    o[i] = 0.f;
+  for (int n = 0; n < NB; ++n) {
+    const float* qp = base + (int64_t)min(q0 + n * 16 + l16, kCtx - 1) * ld3 + 4 * g;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) qf[n][s] = *(const f32x4*)(qp + 16 * s) * kQScaleLog2;
   }
-  float m = -INFINITY, l = 0.f;
-  for (int k0 = 0; k0 < kCtx; k0 += KT) {
-    for (int c = threadIdx.x; c < KT * 64; c += 128) {
-      int key = c >> 6, j = c & 63;
-      int gk = k0 + key;
-      Ksh[key][j] = gk < kCtx ? base[(int64_t)gk * ld3 + d + h * 64 + j] : 0.f;
-      Vsh[key][j] = gk < kCtx ? base[(int64_t)gk * ld3 + 2 * d + h * 64 + j] : 0.f;
-    }
-    __syncthreads();
-    float s[KT];
-    float tmax = -INFINITY;
+  f32x4 o[NB][4];
+  float m[NB], l[NB];
 #pragma unroll
-    for (int k = 0; k < KT; ++k) {
-      float acc = 0.f;
+  for (int n = 0; n < NB; ++n) {
+    m[n] = -INFINITY;
+    l[n] = 0.f;
 #pragma unroll
-      for (int i = 0; i < 64; ++i) acc = fmaf(q[i], Ksh[k][i], acc);
-      s[k] = (k0 + k < kCtx) ? acc : -INFINITY;
-      tmax = fmaxf(tmax, s[k]);
-    }
-    float mnew = fmaxf(m, tmax);
-    float alpha = expf(m - mnew);
-    m = mnew;
-    l *= alpha;
-#pragma unroll
-    for (int i = 0; i < 64; ++i) o[i] *= alpha;
-#pragma unroll
-    for (int k = 0; k < KT; ++k) {
-      float p = expf(s[k] - mnew);
-      l += p;
-#pragma unroll
-      for (int i = 0; i < 64; ++i) o[i] = fmaf(p, Vsh[k][i], o[i]);
-    }
-    __syncthreads();
+    for (int j = 0; j < 4; ++j) o[n][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  if (!qvalid) return;
-  float inv = 1.0f / l;
-  float* op = out + ((int64_t)b * kCtx + qrow) * d + h * 64;
+  f32x4 kf[4], vf[4];
+  auto load = [&](int t) {
+    const float* kp = base + (int64_t)min(t * 16 + l16, kCtx - 1) * ld3 + d + 4 * g;
 #pragma unroll
-  for (int i = 0; i < 64; ++i) op[i] = o[i] * inv;
+    for (int s = 0; s < 4; ++s) kf[s] = *(const f32x4*)(kp + 16 * s);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      vf[r] = *(const f32x4*)(base + (int64_t)min(t * 16 + 4 * g + r, kCtx - 1) * ld3 + 2 * d + 4 * l16);
+  };
+  load(wave);
+  for (int t = wave; t < NT; t += FF_NW) {
+    f32x4 kc[4], vc[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      kc[s] = kf[s];
+      vc[s] = vf[s];
+    }
+    if (t + FF_NW < NT) load(t + FF_NW);
+    f32x4 p[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) p[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+          p[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(kc[s][e], qf[n][s][e], p[n], 0, 0, 0);
+    if (t * 16 + 16 > kCtx) {
+#pragma unroll
+      for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (t * 16 + 4 * g + r >= kCtx) p[n][r] = -INFINITY;
+    }
+    bool moved = false;
+    float mn[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      float x = fmaxf(fmaxf(p[n][0], p[n][1]), fmaxf(p[n][2], p[n][3]));
+      x = fmaxf(x, __shfl_xor(x, 16, 64));
+      x = fmaxf(x, __shfl_xor(x, 32, 64));
+      mn[n] = fmaxf(m[n], x);                      // finite: every tile holds real keys
+      moved |= mn[n] != m[n];
+    }
+    if (__any(moved)) {
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const float f = __builtin_amdgcn_exp2f(m[n] - mn[n]);   // 0 on the first tile
+        m[n] = mn[n];
+        l[n] *= f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[n][j] *= f;
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) p[n][r] = __builtin_amdgcn_exp2f(p[n][r] - m[n]);
+      l[n] += (p[n][0] + p[n][1]) + (p[n][2] + p[n][3]);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+          o[n][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[r][j], p[n][r], o[n][j], 0, 0, 0);
+  }
+  // the wave's record of query l16: lane group g holds dims 16 g .. 16 g + 15
+  // (element r of component j is dim 16 g + 4 r + j)
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    l[n] += __shfl_xor(l[n], 16, 64);
+    l[n] += __shfl_xor(l[n], 32, 64);
+    float* row = osh + (wave * QT + n * 16 + l16) * FF_LD + 16 * g;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      *(f32x4*)(row + 4 * r) = f32x4{o[n][0][r], o[n][1][r], o[n][2][r], o[n][3][r]};
+    if (g == 0) mlsh[wave * QT + n * 16 + l16] = make_float2(m[n], l[n]);
+  }
+  __syncthreads();
+  for (int i = tid; i < QT * 16; i += FF_NW * 64) {
+    const int q = i >> 4, c = (i & 15) * 4;
+    if (q0 + q >= kCtx) break;                     // later items are later queries
+    float2 ml[FF_NW];
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < FF_NW; ++w) {
+      ml[w] = mlsh[w * QT + q];
+      M = fmaxf(M, ml[w].x);
+    }
+    f32x4 num = {0.f, 0.f, 0.f, 0.f};
+    float den = 0.f;
+#pragma unroll
+    for (int w = 0; w < FF_NW; ++w) {
+      const float f = __builtin_amdgcn_exp2f(ml[w].x - M);
+      den = fmaf(f, ml[w].y, den);
+      num += f * *(const f32x4*)(osh + (w * QT + q) * FF_LD + c);
+    }
+    *(f32x4*)(out + ((int64_t)b * kCtx + q0 + q) * d + h * 64 + c) = num * (1.0f / den);
+  }
 }
 
+template <int NB>
+static void launch_flash_f32(const float* qkv, float* out, int B, int n_head, hipStream_t s) {
+  constexpr int QT = 16 * NB;
+  constexpr size_t lds = (size_t)FF_NW * QT * (FF_LD + 2) * sizeof(float);
+  static_assert(lds <= 160 * 1024, "LDS");
+  static const hipError_t attr = hipFuncSetAttribute(
+      (const void*)k_flash_f32<NB>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  (void)attr;
+  k_flash_f32<NB><<<dim3((kCtx + QT - 1) / QT, n_head, B), FF_NW * 64, lds, s>>>(qkv, out, n_head);
+}
+
+// 32 or 48 queries a block: whichever needs less time in rounds of one block
+// per CU, a round costing as much as its queries.  One clip of 6 heads has
+// 282 blocks of 32 (a second round of 26) but 192 of 48.
 void flash_attn_f32(const float* qkv, float* out, int B, int n_head, hipStream_t s) {
   if (B <= 0) return;
-  dim3 grid((kCtx + 127) / 128, n_head, B);
-  k_flash_f32<<<grid, 128, 0, s>>>(qkv, out, n_head);
+  auto cost = [&](int nb) {
+    const int64_t blocks = (int64_t)((kCtx + 16 * nb - 1) / (16 * nb)) * n_head * B;
+    return (blocks + 255) / 256 * nb;
+  };
+  if (cost(3) < cost(2))
+    launch_flash_f32<3>(qkv, out, B, n_head, s);
+  else
+    launch_flash_f32<2>(qkv, out, B, n_head, s);
 }
 
 // ---------------------------------------------------------------------------
