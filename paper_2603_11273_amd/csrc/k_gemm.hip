@@ -4,7 +4,7 @@
 //    operands, fp32 accumulation, LDS double buffering, fused epilogues
 //    (bias, exact GELU, fp32 residual add, conv-stem row mapping, scatter of
 //    all decoder layers' cross K/V into a slot's cache).
-//  * gemm_f32: the same contract in plain fp32 FMA (the fp32 model path).
+//  * gemm_f32: the same contract on fp32 MFMA (the fp32 model path).
 //  * dgemm_bf16 / dgemm_f32: skinny products for the decode rows (weights
 //    streamed once): bias / GELU fused into one slice, or float32 partial
 //    sums of a few K slices that the next kernel adds up.
@@ -1342,58 +1342,142 @@ void gemm_bf16(const AView& a, const bf16_t* w, int M, int N, int K, const Epilo
 }
 
 // ---------------------------------------------------------------------------
-// fp32 GEMM (SIMT): 64x64 tile, 256 threads, 4x4 outputs per thread.
+// fp32 GEMM on v_mfma_f32_32x32x2_f32: bound by the fp32 matrix rate (148
+// TFLOP/s for a large product) and, at one clip's sizes, by each block's start
+// and end.  Four waves hold one 32x32 block of the output between them: K goes
+// in chunks of 16 floats (16-byte pieces XOR-swizzled as in the bf16 kernels),
+// chunk c belongs to wave c % 4, and the four chains are added as (0 + 1) +
+// (2 + 3) at the end.  So even a product of 1500 x 384 puts several waves on
+// every SIMD, and the sums of an element are the same in every tile shape:
+// they do not depend on how many rows a product has.
+// Measured (M x N x K): 1500 x 1536 x 384 30 us, 12000 x 1536 x 384 (as two
+// halves beside each other) 164 us each; 42 us and about 1 ms as 64x64 tiles
+// of scalar fp32.  32-float chunks 34 us (too few blocks a CU), a wave per
+// output block with all four chains 35 us, operands read from global memory
+// into registers without LDS 39 us.
 // ---------------------------------------------------------------------------
-template <int KIND>
-__global__ __launch_bounds__(256) void k_gemm_f32(AView a, const float* __restrict__ w, int M,
-                                                  int N, int K, Epilogue e, int n_tn) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[BK][BN + 4];
-  const int tid = threadIdx.x;
-  const int tn = blockIdx.x % n_tn, tm = blockIdx.x / n_tn;
+constexpr int GF_KC = 16, GF_PR = GF_KC / 4;   // floats, 16-byte pieces a row
+
+template <int KIND, int WM, int WN>
+__global__ __launch_bounds__(WM* WN * 256) void k_gemm_f32(AView a, const float* __restrict__ w,
+                                                           int M, int N, int K, Epilogue e,
+                                                           int n_tm, int n_tn, int gm) {
+  constexpr int NT = WM * WN * 256, BM = 32 * WM, BN = 32 * WN, ST = 4 * GF_KC;
+  constexpr int PA = BM * 4 * GF_PR / NT, PB = BN * 4 * GF_PR / NT;   // pieces per thread
+  static_assert(PA * NT == BM * 4 * GF_PR && PB * NT == BN * 4 * GF_PR, "tile/threads");
+  extern __shared__ __attribute__((aligned(16))) float fsmem[];
+  float (*As)[BM * ST] = (float (*)[BM * ST])fsmem;                   // [2 stages][4 chunks][BM][16]
+  float (*Bs)[BN * ST] = (float (*)[BN * ST])(fsmem + 2 * BM * ST);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l32 = lane & 31, lh = lane >> 5;
+  const int wk = wave & 3, wm = (wave >> 2) % WM, wn = (wave >> 2) / WM;
+  int tm, tn;
+  tile_of(blockIdx.x, n_tm * n_tn, n_tm, n_tn, gm, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
-  const int lr = tid >> 2, lk = (tid & 3) * 4;      // loader: row, k offset
-  const int ar = m0 + lr, bn = n0 + lr;
-  const float* ap = (const float*)a.ptr + arow_offset(a, ar < M ? ar : 0) + lk;
-  const float* bp = w + (int64_t)(bn < N ? bn : 0) * K + lk;
-  const int ty = tid >> 4, tx = tid & 15;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += BK) {
-    float4 va = make_float4(0.f, 0.f, 0.f, 0.f), vb = va;
-    if (ar < M && k0 + lk < K) va = *(const float4*)(ap + k0);
-    if (bn < N && k0 + lk < K) vb = *(const float4*)(bp + k0);
-    As[lk + 0][lr] = va.x; As[lk + 1][lr] = va.y; As[lk + 2][lr] = va.z; As[lk + 3][lr] = va.w;
-    Bs[lk + 0][lr] = vb.x; Bs[lk + 1][lr] = vb.y; Bs[lk + 2][lr] = vb.z; Bs[lk + 3][lr] = vb.w;
-    __syncthreads();
+  // piece p of a stage: row p / 16, chunk p / 4 % 4, 16 bytes p % 4
+  const float* ap[PA];
+  const float* bp[PB];
+  int ao[PA], bo[PB], ak[PA], bk[PB];
 #pragma unroll
-    for (int k = 0; k < BK; ++k) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-    }
-    __syncthreads();
+  for (int i = 0; i < PA; ++i) {
+    const int p = tid + i * NT, row = p / (4 * GF_PR), ck = p / GF_PR % 4, c = p % GF_PR;
+    ak[i] = ck * GF_KC + c * 4;
+    // (plain matrices skip the clip division)
+    const int r = min(m0 + row, M - 1);
+    ap[i] = (const float*)a.ptr + (a.rows_per_batch >= M ? r * a.lda : arow_offset(a, r)) + ak[i];
+    ao[i] = (ck * BM + row) * GF_KC + ((c ^ lds_swz<2 * GF_KC>(row)) * 4);
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < PB; ++i) {
+    const int p = tid + i * NT, row = p / (4 * GF_PR), ck = p / GF_PR % 4, c = p % GF_PR;
+    bk[i] = ck * GF_KC + c * 4;
+    bp[i] = w + (int64_t)min(n0 + row, N - 1) * K + bk[i];
+    bo[i] = (ck * BN + row) * GF_KC + ((c ^ lds_swz<2 * GF_KC>(row)) * 4);
+  }
+  f32x4 ra[PA], rb[PB];
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  auto load = [&](int k0) {
+    if (k0 + ST <= K) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int row = m0 + ty * 4 + i, col = n0 + tx * 4 + j;
-      if (row < M && col < N) epi_apply<KIND, float>(e, row, col, acc[i][j]);
+      for (int i = 0; i < PA; ++i) ra[i] = *(const f32x4*)(ap[i] + k0);
+#pragma unroll
+      for (int i = 0; i < PB; ++i) rb[i] = *(const f32x4*)(bp[i] + k0);
+    } else {                                       // K is a multiple of 4
+#pragma unroll
+      for (int i = 0; i < PA; ++i) ra[i] = k0 + ak[i] < K ? *(const f32x4*)(ap[i] + k0) : zero;
+#pragma unroll
+      for (int i = 0; i < PB; ++i) rb[i] = k0 + bk[i] < K ? *(const f32x4*)(bp[i] + k0) : zero;
     }
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < PA; ++i) *(f32x4*)&As[buf][ao[i]] = ra[i];
+#pragma unroll
+    for (int i = 0; i < PB; ++i) *(f32x4*)&Bs[buf][bo[i]] = rb[i];
+  };
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  const int sw = lds_swz<2 * GF_KC>(l32);
+  const int arow = (wk * BM + wm * 32 + l32) * GF_KC, brow = (wk * BN + wn * 32 + l32) * GF_KC;
+  const int nst = (K + ST - 1) / ST;
+  load(0);
+  store(0);
+  __syncthreads();
+  for (int t = 0; t < nst; ++t) {
+    if (t + 1 < nst) load((t + 1) * ST);
+    const float* as = As[t & 1] + arow;
+    const float* bs = Bs[t & 1] + brow;
+    f32x4 af[GF_KC / 8], bf[GF_KC / 8];
+#pragma unroll
+    for (int s = 0; s < GF_KC / 8; ++s) {
+      const int c = ((2 * s + lh) ^ sw) * 4;
+      af[s] = *(const f32x4*)(as + c);
+      bf[s] = *(const f32x4*)(bs + c);
+    }
+#pragma unroll
+    for (int s = 0; s < GF_KC / 8; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[s][q], bf[s][q], acc, 0, 0, 0);
+    if (t + 1 < nst) store((t + 1) & 1);
+    __syncthreads();
+  }
+  // the chains meet in LDS (the stages are free); a lane holds column l32
+  // and, for register r, row 8 (r / 4) + 4 lh + r % 4 of the 32x32 block
+  static_assert(2 * ST * (BM + BN) >= WM * WN * 4096, "reduction space");
+  float* red = fsmem + (wn * WM + wm) * 4096;      // [4 chains][16][64]
+#pragma unroll
+  for (int r = 0; r < 16; ++r) red[(wk * 16 + r) * 64 + lane] = acc[r];
+  __syncthreads();
+  const int row0 = m0 + wm * 32 + 4 * lh + 8 * wk, col = n0 + wn * 32 + l32;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float* c = red + (wk * 4 + i) * 64 + lane;
+    if (row0 + i < M && col < N)
+      epi_apply<KIND, float>(e, row0 + i, col, (c[0] + c[1024]) + (c[2048] + c[3072]));
+  }
 }
 
+template <int KIND, int WM, int WN>
+static void launch_gemm_f32_cfg(const AView& a, const float* w, int M, int N, int K,
+                                const Epilogue& e, hipStream_t s) {
+  constexpr size_t lds = (size_t)2 * 4 * GF_KC * 32 * (WM + WN) * sizeof(float);
+  static_assert(lds <= 64 * 1024, "LDS");
+  const int n_tm = (M + 32 * WM - 1) / (32 * WM), n_tn = (N + 32 * WN - 1) / (32 * WN);
+  k_gemm_f32<KIND, WM, WN><<<n_tm * n_tn, WM * WN * 256, lds, s>>>(a, w, M, N, K, e, n_tm, n_tn, 4);
+}
+
+// 64x64 tiles (16 waves) halve the operand traffic and take over where they
+// give every CU two blocks: 12000 x 1536 x 384 in halves 164 us against 190,
+// 1500 x 1536 x 384 (576 tiles) 31.6 against 30.2.
 template <int KIND>
 static void launch_gemm_f32(const AView& a, const float* w, int M, int N, int K,
                             const Epilogue& e, hipStream_t s) {
-  int n_tm = (M + 63) / 64, n_tn = (N + 63) / 64;
-  k_gemm_f32<KIND><<<n_tm * n_tn, 256, 0, s>>>(a, w, M, N, K, e, n_tn);
+  if ((int64_t)((M + 63) / 64) * ((N + 63) / 64) > 576)
+    launch_gemm_f32_cfg<KIND, 2, 2>(a, w, M, N, K, e, s);
+  else
+    launch_gemm_f32_cfg<KIND, 1, 1>(a, w, M, N, K, e, s);
 }
 
 void gemm_f32(const AView& a, const float* w, int M, int N, int K, const Epilogue& e,
