@@ -20,7 +20,7 @@ LIB = os.path.join(HERE, "libasr_mi355x.so")
 SYNTH_LIB = os.path.join(HERE, "libasr_synth.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 
-HIP_SOURCES = ["k_misc.hip", "k_gemm.hip", "k_attn.hip", "runtime.hip"]
+HIP_SOURCES = ["k_misc.hip", "k_gemm.hip", "k_attn.hip", "k_rows.hip", "runtime.hip"]
 CPP_SOURCES = ["queue.cpp", "serve.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed fp32 instructions are disabled: hipcc emits them from plain float

@@ -91,11 +91,153 @@ __device__ __forceinline__ float wave_sum_lanes(float v) {
   const auto p32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
   return __uint_as_float(p32[0]) + __uint_as_float(p32[1]);
 }
+// Sum over each group of eight lanes (every lane ends with its group's).
+__device__ __forceinline__ float group8_sum_lanes(float v) {
+  v = ASR_DPP_ADD(v, 0xB1);    // quad_perm [1,0,3,2]
+  v = ASR_DPP_ADD(v, 0x4E);    // quad_perm [2,3,0,1]
+  return ASR_DPP_ADD(v, 0x141);   // row_half_mirror
+}
+// Sum over the eight lanes that share lane % 8.
+__device__ __forceinline__ float stride8_sum_lanes(float v) {
+  v = ASR_DPP_ADD(v, 0x128);   // row_ror:8
+  const uint32_t u = __float_as_uint(v);
+  const auto p16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  v = __uint_as_float(p16[0]) + __uint_as_float(p16[1]);
+  const uint32_t w = __float_as_uint(v);
+  const auto p32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return __uint_as_float(p32[0]) + __uint_as_float(p32[1]);
+}
+// Maximum over the eight lanes that share lane % 8.
+__device__ __forceinline__ float stride8_max_lanes(float v) {
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, true)));
+  const uint32_t u = __float_as_uint(v);
+  const auto p16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  v = fmaxf(__uint_as_float(p16[0]), __uint_as_float(p16[1]));
+  const uint32_t w = __float_as_uint(v);
+  const auto p32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return fmaxf(__uint_as_float(p32[0]), __uint_as_float(p32[1]));
+}
 #undef ASR_DPP_ADD
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
+}
+
+// ---------------------------------------------------------------------------
+// Direct global -> LDS loads and their waits
+// ---------------------------------------------------------------------------
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
+}
+
+template <int MAXN>
+__device__ __forceinline__ void wait_vmcnt_rt(int n) {
+  // n is wave-uniform; the immediate must be a constant
+  if constexpr (MAXN > 0) {
+    if (n >= MAXN) { wait_vmcnt<MAXN>(); return; }
+    wait_vmcnt_rt<MAXN - 1>(n);
+  } else {
+    wait_vmcnt<0>();
+  }
+}
+constexpr int kWaitLgkm0 = 0xF | (0x3 << 14) | (0x7 << 4);   // s_waitcnt lgkmcnt(0) alone
+
+__device__ __forceinline__ void lds_dma16(uint32_t lds_addr, const void* gptr) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+               :: "s"(lds_addr), "v"(gptr) : "memory", "m0");
+}
+// Same with a wave-uniform 64-bit base in SGPRs and a 32-bit per-lane byte
+// offset: no per-load address arithmetic in vector registers.
+__device__ __forceinline__ void lds_dma16_s(uint32_t lds_addr, uint32_t voff, const void* sbase) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(lds_addr), "v"(voff), "s"(sbase) : "memory", "m0");
+}
+
+// ---------------------------------------------------------------------------
+// Decode rows
+// ---------------------------------------------------------------------------
+// LayerNorm of one float32 row by one wave (d a multiple of 64, at most
+// 256 NV; biased variance, eps 1e-5): one definition for every kernel of a
+// decode step, so a row's values do not depend on which of them forms it.
+// Gain and shift are loaded with the row, ahead of the reductions.
+template <int NV>
+struct RowLN {
+  float4 v[NV], g[NV], b[NV];
+  __device__ __forceinline__ void params(const float* gain, const float* shift, int d, int lane) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int e = min((lane + 64 * i) * 4, d - 4);
+      g[i] = *(const float4*)(gain + e);
+      b[i] = *(const float4*)(shift + e);
+    }
+  }
+  __device__ __forceinline__ void row(const float* p, int d, int lane) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) v[i] = *(const float4*)(p + min((lane + 64 * i) * 4, d - 4));
+  }
+  template <typename T>
+  __device__ __forceinline__ void write(T* out, int d, int lane) {
+    const float inv = 1.0f / d;
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      if ((lane + 64 * i) * 4 < d) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+    const float mean = wave_sum_lanes(s) * inv;
+    float q = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      if ((lane + 64 * i) * 4 < d) {
+        v[i] = make_float4(v[i].x - mean, v[i].y - mean, v[i].z - mean, v[i].w - mean);
+        q += (v[i].x * v[i].x + v[i].y * v[i].y) + (v[i].z * v[i].z + v[i].w * v[i].w);
+      }
+    const float rstd = rsqrtf(wave_sum_lanes(q) * inv + 1e-5f);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int e = (lane + 64 * i) * 4;
+      if (e < d)
+        St<T>::st4(out, e, make_float4(v[i].x * rstd * g[i].x + b[i].x, v[i].y * rstd * g[i].y + b[i].y,
+                                       v[i].z * rstd * g[i].z + b[i].z, v[i].w * rstd * g[i].w + b[i].w));
+    }
+  }
+};
+
+// Sum of N values (a power of two) as a balanced tree.
+template <int N, class F>
+__device__ __forceinline__ f32x4 tree_sum(int first, F&& get) {
+  if constexpr (N == 1) {
+    return get(first);
+  } else {
+    const f32x4 a = tree_sum<N / 2>(first, get);
+    return a + tree_sum<N / 2>(first + N / 2, get);
+  }
+}
+
+// Cross attention of (row, head) `rh` from its key chunks' records: out =
+// sum_c e^{m_c - M} acc_c / sum_c e^{m_c - M} l_c, M = max_c m_c; lane = dim.
+template <typename T>
+__device__ __forceinline__ float cross_merge(const float* part, int64_t rh, int lane) {
+  constexpr int NCH = kCrossChunks<T>;
+  const float* rec = part + rh * NCH * DA_REC;
+  float m[NCH], l[NCH], a[NCH], M = -INFINITY;
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    m[c] = rec[c * DA_REC];
+    l[c] = rec[c * DA_REC + 1];
+    a[c] = rec[c * DA_REC + 2 + lane];
+  }
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) M = fmaxf(M, m[c]);
+  float num = 0.f, den = 0.f;
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    const float f = expf(m[c] - M);
+    den += f * l[c];
+    num += f * a[c];
+  }
+  return num / den;
 }
 
 // Total order on floats as unsigned integers (larger float -> larger key).

@@ -74,25 +74,38 @@ void gemm_f32(const AView& a, const float* w, int M, int N, int K, const Epilogu
 // Number of CUs the persistent bf16 GEMM leaves free (process-wide; 0 = none).
 void gemm_set_cu_reserve(int n);
 
-// Skinny GEMM for decode rows (D <= 128, N % 32 == 0, K % 64 == 0), x [D][K]
-// times w [N][K]^T.  DG_PARTIAL: out = float32 partial sums over K slices,
-// partial[s][b][n] for s < dgemm_splits(N, K) (returned); DG_BIAS / DG_GELU:
-// out[b][n] = (gelu)(sum + bias[n]) in bf16 (returns 1).
-enum DgEpi : int32_t { DG_PARTIAL = 0, DG_BIAS = 1, DG_GELU = 2 };
-int dgemm_bf16(const bf16_t* x, const bf16_t* w, int D, int N, int K, int epi,
-               const float* bias, void* out, hipStream_t s);
-int dgemm_splits(int N, int K);
-// fp32 path: out[b][n] = sum_k x[b][k] w[n][k] (one partial slice, no bias).
-void dgemm_f32(const float* x, const float* w, int D, int N, int K, float* out, hipStream_t s);
-// out = epilogue(sum_s partial[s] + bias): mode 0 store (T), 1 gelu (T), 2 residual add (f32).
+// Products of the decode rows (D <= 128 rows, N a multiple of 64, K a multiple
+// of 64 and at most 2048 where rows are prepared); the sums of a row do not
+// depend on D, nor on which of these forms them.
+enum RowsX : int { RX_MEM = 0, RX_LN = 1, RX_MERGE = 2 };        // where x comes from
+enum RowsEpi : int { RE_F32 = 0, RE_GELU = 1, RE_RESID = 2 };
+constexpr int kFewRows = 32;
+// out[b][n] = LayerNorm(h[b]; g, beta) . w[n] + bias[n] in float32, or its GELU
+// in storage type T.
 template <typename T>
-void dgemm_reduce(const float* partial, int splits, int D, int N, const float* bias, int mode,
-                  void* out, hipStream_t s);
-
-// h[b] += bias + sum_s partial[s][b]; xn[b] = LayerNorm(h[b]) with (g, beta).  d <= 2048.
+void rows_ln(const float* h, const float* g, const float* beta, const T* w, const float* bias, int D,
+             int N, int K, bool gelu, void* out, hipStream_t s);
+// The same of given rows x.
 template <typename T>
-void reduce_resid_ln(const float* partial, int splits, int D, int d, const float* bias, float* h,
-                     const float* g, const float* beta, T* xn, hipStream_t s);
+void rows_mem(const T* x, const T* w, const float* bias, int D, int N, int K, bool gelu, void* out,
+              hipStream_t s);
+// h[b][n] += x[b] . w[n] + bias[n].
+template <typename T>
+void rows_resid(const T* x, const T* w, const float* bias, int D, int N, int K, float* h,
+                hipStream_t s);
+// The same for x[b] = the cross attention merged from its records.
+template <typename T>
+void rows_merge_resid(const float* rec, const T* w, const float* bias, int D, int d, float* h,
+                      hipStream_t s);
+// out[b] = LayerNorm(h[b]; g, beta).
+template <typename T>
+void rows_norm(const float* h, int D, int d, const float* g, const float* beta, T* out,
+               hipStream_t s);
+// rows_resid, then rows_norm into xn, for many rows (part: rows_part_floats).
+void rows_resid_norm(const bf16_t* x, const bf16_t* w, const float* bias, int D, int d, int K,
+                     float* h, const float* g, const float* beta, bf16_t* xn, float* part,
+                     hipStream_t s);
+size_t rows_part_floats(int D, int d);
 
 // Vocabulary projection fused with argmax: keys[b][tile] (ordered value, lowest index).
 void vocab_argmax_bf16(const bf16_t* x, const bf16_t* emb, int D, int V, int K,
@@ -130,26 +143,24 @@ void flash_attn_bf16(const bf16_t* qkv, const bf16_t* vt, bf16_t* out, int B, in
 void flash_attn_f32(const float* qkv, float* out, int B, int n_head, hipStream_t s);
 
 // Decode attention.  Self: writes k, v of each row at its slot position, then
-// attends over position + 1 keys.  Cross: attends over 1500 cached keys.
-// Keys are split into chunks handled by separate blocks; `part` (at least
-// decode_attn_part_floats(D, n_head) floats) holds the per-chunk partials
-// that a combine kernel merges into out.
-constexpr int DA_NCH = 4;    // chunks per row at most (1500 cross keys / 384)
-constexpr int DA_REC = 66;   // floats per partial: max, sum, 64 weighted values
+// attends over position + 1 keys; q, k, v of the step are float32 qkv [D][3d].
+// Cross: q float32 [D][d], attends over 1500 cached keys, which are split into
+// chunks handled by separate blocks; each leaves a record (max, sum, 64
+// weighted values) in `part` (at least decode_attn_part_floats(D, n_head)
+// floats), merged by rows_merge_resid or decode_cross_merge.
+constexpr int DA_REC = 66;   // floats per record
+template <typename T>
+constexpr int kCrossChunks = sizeof(T) == 2 ? 4 : 8;
 int decode_attn_part_floats(int D, int n_head);
-// Self: fp32 contexts read q, k, v from the fused QKV output qkv [D][3d];
-// bf16 contexts from the float32 partial sums of the QKV product plus its
-// bias (qkv_part[s][b][3d], s < qkv_splits).
 template <typename T>
-void decode_self_attn(const T* qkv, const float* qkv_part, int qkv_splits, const float* qkv_bias,
-                      T* cache, int64_t slot_stride, int64_t layer_off, const int32_t* slots,
-                      const int32_t* pos, int D, int n_head, T* out, float* part, hipStream_t s);
-// The cross attention takes its queries as the float32 partial sums of the
-// query product: q[b] = bias + sum_{s < q_splits} q_part[s][b].
+void decode_self_attn(const float* qkv, T* cache, int64_t slot_stride, int64_t layer_off,
+                      const int32_t* slots, const int32_t* pos, int D, int n_head, T* out,
+                      hipStream_t s);
 template <typename T>
-void decode_cross_attn(const float* q_part, int q_splits, const float* q_bias, T* cache,
-                       int64_t slot_stride, int64_t layer_off, const int32_t* slots, int D,
-                       int n_head, T* out, float* part, hipStream_t s);
+void decode_cross_attn(const float* q, const T* cache, int64_t slot_stride, int64_t layer_off,
+                       const int32_t* slots, int D, int n_head, float* part, hipStream_t s);
+template <typename T>
+void decode_cross_merge(const float* part, int D, int n_head, T* out, hipStream_t s);
 
 template <typename T>
 void embed(const T* tok_emb, const float* pos_emb, const int32_t* tokens, const int32_t* pos,

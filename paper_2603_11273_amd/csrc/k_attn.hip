@@ -524,208 +524,58 @@ void flash_attn_f32(const float* qkv, float* out, int B, int n_head, hipStream_t
 // ---------------------------------------------------------------------------
 // Decode attention
 // ---------------------------------------------------------------------------
-// Loads 8 consecutive head dims of one key/value row as floats.
-__device__ __forceinline__ void load8(const float* p, float* v) {
-  float4 a = *(const float4*)p, c = *(const float4*)(p + 4);
-  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-  v[4] = c.x; v[5] = c.y; v[6] = c.z; v[7] = c.w;
-}
-__device__ __forceinline__ void load8(const bf16_t* p, float* v) {
-  uint4 u = *(const uint4*)p;
-  v[0] = __uint_as_float(u.x << 16); v[1] = __uint_as_float(u.x & 0xffff0000u);
-  v[2] = __uint_as_float(u.y << 16); v[3] = __uint_as_float(u.y & 0xffff0000u);
-  v[4] = __uint_as_float(u.z << 16); v[5] = __uint_as_float(u.z & 0xffff0000u);
-  v[6] = __uint_as_float(u.w << 16); v[7] = __uint_as_float(u.w & 0xffff0000u);
-}
+// Eight consecutive head dims of one key / value row, in storage type.
+template <typename T>
+struct Row8;
+template <>
+struct Row8<float> {
+  float4 a, c;
+  __device__ __forceinline__ void keep(bool ok) {
+    if (!ok) a = c = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  // at byte offset `off` of a wave-uniform base
+  __device__ __forceinline__ void load(const float* p, uint32_t off) {
+    a = *(const float4*)((const char*)p + off);
+    c = *(const float4*)((const char*)p + off + 16);
+  }
+  __device__ __forceinline__ void get(float* v) const {
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+    v[4] = c.x; v[5] = c.y; v[6] = c.z; v[7] = c.w;
+  }
+};
+template <>
+struct Row8<bf16_t> {
+  uint4 u;
+  __device__ __forceinline__ void keep(bool ok) {
+    if (!ok) u = uint4{0u, 0u, 0u, 0u};
+  }
+  __device__ __forceinline__ void load(const bf16_t* p, uint32_t off) {
+    u = *(const uint4*)((const char*)p + off);
+  }
+  __device__ __forceinline__ void get(float* v) const {
+    v[0] = __uint_as_float(u.x << 16); v[1] = __uint_as_float(u.x & 0xffff0000u);
+    v[2] = __uint_as_float(u.y << 16); v[3] = __uint_as_float(u.y & 0xffff0000u);
+    v[4] = __uint_as_float(u.z << 16); v[5] = __uint_as_float(u.z & 0xffff0000u);
+    v[6] = __uint_as_float(u.w << 16); v[7] = __uint_as_float(u.w & 0xffff0000u);
+  }
+};
 
-// Block of 256 threads; lane group of 8 lanes per key (8 dims each), 4 waves
-// x 8 keys = 32 keys per pass, 4 passes unrolled per loop iteration.
-// Keys per block of the decode attention: a row's keys are split into chunks
-// of DA_CK handled by separate blocks (flash-decoding), which fills the chip
-// in whole rounds (128 rows x 20 heads x 4 chunks of the 1500 cross keys =
-// 10240 blocks = 5 rounds of 2048 resident blocks); a combine kernel merges
-// the chunks' (max, sum, weighted values).
-constexpr int DA_CK = 384;
-
-// SELF: queries, keys and values of the step come from the fused QKV output
-// `src` [D][3d].  Cross: the query is bias + the q_splits float32 partial
-// sums of the query product (q_part[s][row][d]).
-template <typename T, bool SELF>
-__global__ __launch_bounds__(256) void k_decode_attn(const T* __restrict__ src,
-                                                     const float* __restrict__ q_part,
-                                                     int q_splits, const float* __restrict__ q_bias,
-                                                     int D, T* cache,
+// Decode cross attention: one block per (row, head, chunk of the 1500 keys).
+// Each thread issues the loads of its share of the chunk's keys (8 lanes per
+// key, 32 keys per pass, NP passes), K and V, before any arithmetic, so the
+// value stream's latency hides behind the scores and the softmax; scores stay
+// in registers (one cross-lane reduction per key), and three block barriers
+// remain.  The block leaves a (max, sum, weighted values) record.
+template <typename T>
+__global__ __launch_bounds__(256) void k_dattn_cross(const float* __restrict__ q,
+                                                     const T* __restrict__ cache,
                                                      int64_t slot_stride, int64_t layer_off,
-                                                     const int32_t* slots, const int32_t* pos,
-                                                     int n_head, float* __restrict__ part) {
-  constexpr int CTX = SELF ? kTextCtx : kCtx;
-  __shared__ float qs[64];
-  __shared__ float sc[DA_CK];
-  __shared__ float red[4];
-  __shared__ float ored[4][64];
-  const int h = blockIdx.x, row = blockIdx.y, chunk = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int d = n_head * 64;
-  const int ldsrc = 3 * d;
-  const int n = SELF ? pos[row] + 1 : kCtx;
-  const int k0 = chunk * DA_CK;
-  if (k0 >= n) return;                          // this row has fewer chunks (uniform per block)
-  const int kn = min(DA_CK, n - k0);            // keys of this chunk
-  const int slot = slots[row];
-  T* kb = cache + (int64_t)slot * slot_stride + layer_off + (int64_t)h * CTX * 64;
-  T* vb = kb + (int64_t)n_head * CTX * 64;
-  const T* srow = SELF ? src + (int64_t)row * ldsrc + h * 64 : nullptr;
-
-  if (tid < 64) {
-    if constexpr (SELF) {
-      qs[tid] = St<T>::ld(srow, tid) * 0.125f;
-    } else {
-      const int c = h * 64 + tid;
-      float v = q_bias[c];
-      for (int sp = 0; sp < q_splits; ++sp) v += q_part[((int64_t)sp * D + row) * d + c];
-      qs[tid] = v * 0.125f;
-    }
-  }
-  if (SELF && tid < 128 && n - 1 >= k0 && n - 1 < k0 + kn) {
-    // the chunk holding position n-1 stores this step's k, v there
-    int j = tid & 63;
-    if (tid < 64)
-      kb[(int64_t)(n - 1) * 64 + j] = srow[d + j];
-    else
-      vb[(int64_t)(n - 1) * 64 + j] = srow[2 * d + j];
-  }
-  __syncthreads();
-
-  const int sub = lane >> 3, dc = (lane & 7) * 8;
-  float qv[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) qv[i] = qs[dc + i];
-
-  // scores of the chunk's keys (8 lanes per key, 16-byte loads)
-  for (int g0 = 0; g0 < kn; g0 += 128) {
-    float partial[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int kk = g0 + u * 32 + wave * 8 + sub, key = k0 + kk;
-      partial[u] = 0.f;
-      if (kk < kn) {
-        const T* kp = (SELF && key == n - 1) ? (srow + d) : (kb + (int64_t)key * 64);
-        float kv[8];
-        load8(kp + dc, kv);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) partial[u] = fmaf(qv[i], kv[i], partial[u]);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      float p = partial[u];
-      p += __shfl_xor(p, 1, 64);
-      p += __shfl_xor(p, 2, 64);
-      p += __shfl_xor(p, 4, 64);
-      const int kk = g0 + u * 32 + wave * 8 + sub;
-      if ((lane & 7) == 0 && kk < kn) sc[kk] = p;
-    }
-  }
-  __syncthreads();
-
-  float mx = -INFINITY;
-  for (int k = tid; k < kn; k += 256) mx = fmaxf(mx, sc[k]);
-  mx = wave_max(mx);
-  if (lane == 0) red[wave] = mx;
-  __syncthreads();
-  mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  __syncthreads();
-  float sum = 0.f;
-  for (int k = tid; k < kn; k += 256) {
-    float p = expf(sc[k] - mx);
-    sc[k] = p;
-    sum += p;
-  }
-  sum = wave_sum(sum);
-  if (lane == 0) red[wave] = sum;
-  __syncthreads();
-  const float l = red[0] + red[1] + red[2] + red[3];
-
-  // probability-weighted values of the chunk
-  float acc[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-  for (int g0 = 0; g0 < kn; g0 += 128) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int kk = g0 + u * 32 + wave * 8 + sub, key = k0 + kk;
-      if (kk < kn) {
-        const T* vp = (SELF && key == n - 1) ? (srow + 2 * d) : (vb + (int64_t)key * 64);
-        float vv[8];
-        load8(vp + dc, vv);
-        const float p = sc[kk];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = fmaf(p, vv[i], acc[i]);
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    float a = acc[i];
-    a += __shfl_xor(a, 8, 64);
-    a += __shfl_xor(a, 16, 64);
-    a += __shfl_xor(a, 32, 64);
-    acc[i] = a;
-  }
-  if (lane < 8) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) ored[wave][dc + i] = acc[i];
-  }
-  __syncthreads();
-  // partial record of (row, head, chunk): [max, sum, 64 weighted values]
-  float* rec = part + (((int64_t)row * n_head + h) * DA_NCH + chunk) * DA_REC;
-  if (tid < 64) rec[2 + tid] = ored[0][tid] + ored[1][tid] + ored[2][tid] + ored[3][tid];
-  if (tid == 0) {
-    rec[0] = mx;
-    rec[1] = l;
-  }
-}
-
-// out[row][h] = sum_c e^{m_c - M} acc_c / sum_c e^{m_c - M} l_c over the
-// row's chunks (M = max_c m_c).  One wave per (row, head).
-template <typename T, bool SELF>
-__global__ __launch_bounds__(256) void k_decode_combine(const float* __restrict__ part,
-                                                        const int32_t* pos, int D, int n_head,
-                                                        T* __restrict__ out) {
-  const int w = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (w >= D * n_head) return;
-  const int row = w / n_head, h = w - row * n_head;
-  const int n = SELF ? pos[row] + 1 : kCtx;
-  const int nch = (n + DA_CK - 1) / DA_CK;
-  const float* rec = part + (int64_t)w * DA_NCH * DA_REC;
-  float M = -INFINITY;
-  for (int c = 0; c < nch; ++c) M = fmaxf(M, rec[c * DA_REC]);
-  float num = 0.f, den = 0.f;
-  for (int c = 0; c < nch; ++c) {
-    const float f = expf(rec[c * DA_REC] - M);
-    den += f * rec[c * DA_REC + 1];
-    num += f * rec[c * DA_REC + 2 + lane];
-  }
-  St<T>::st(out, (int64_t)row * n_head * 64 + h * 64 + lane, num / den);
-}
-
-// bf16 decode cross attention with every K and V row of the block's keys
-// in flight at once: each thread issues the 16-byte loads of its share of
-// all keys (8 lanes per key, 32 keys per pass, NP passes) for K and V before
-// any arithmetic, so the value stream's latency hides behind the scores and
-// the softmax; scores stay in registers (one cross-lane reduction per key),
-// and three block barriers remain.  The query is the bias plus the qp_splits
-// float32 partial sums of its product (qp[s][row][d]).  One block per (row,
-// head, 384-key chunk), leaving a (max, sum, weighted values) record for
-// the combine kernel.
-template <int NP>
-__global__ __launch_bounds__(256) void k_dattn_cross_bf16(const float* __restrict__ qp, int qp_splits,
-                                                          const float* __restrict__ qp_bias, int D,
-                                                          const bf16_t* cache, int64_t slot_stride,
-                                                          int64_t layer_off, const int32_t* slots,
-                                                          int n_head, float* __restrict__ part) {
-  constexpr int CK = NP * 32;                       // keys per block
-  __shared__ float qs[64];
+                                                     const int32_t* __restrict__ slots, int n_head,
+                                                     float* __restrict__ part) {
+  constexpr int NCH = kCrossChunks<T>, NP = 48 / NCH;   // 32 * 48 = 1536 keys
+  constexpr int CK = NP * 32;
+  static_assert(CK * NCH >= kCtx && CK * (NCH - 1) < kCtx, "chunks cover the keys");
+  __shared__ __attribute__((aligned(16))) float qs[64];
   __shared__ float red[2][4];
   __shared__ float ored[4][64];
   const int h = blockIdx.x, row = blockIdx.y, chunk = blockIdx.z;
@@ -733,30 +583,20 @@ __global__ __launch_bounds__(256) void k_dattn_cross_bf16(const float* __restric
   const int d = n_head * 64;
   const int k0 = chunk * CK;
   const int kn = min(CK, kCtx - k0);
-  const int slot = slots[row];
-  const bf16_t* kb = cache + (int64_t)slot * slot_stride + layer_off + (int64_t)h * kCtx * 64;
-  const bf16_t* vb = kb + (int64_t)n_head * kCtx * 64;
   const int sub = lane >> 3, dc = (lane & 7) * 8;
+  const T* kb = cache + (int64_t)slots[row] * slot_stride + layer_off + (int64_t)h * kCtx * 64;
+  const T* vb = kb + (int64_t)n_head * kCtx * 64;
 
-  // all loads of the block's keys first
-  uint4 kr[NP], vr[NP];
-  const uint4 zero = {0u, 0u, 0u, 0u};
+  // all loads of the block's keys first, without a branch (past the chunk the
+  // last key again, not used)
+  Row8<T> kr[NP], vr[NP];
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
-    const int kk = p * 32 + wave * 8 + sub, key = k0 + kk;
-    kr[p] = zero;
-    vr[p] = zero;
-    if (kk < kn) {
-      kr[p] = *(const uint4*)(kb + (int64_t)key * 64 + dc);
-      vr[p] = *(const uint4*)(vb + (int64_t)key * 64 + dc);
-    }
+    const uint32_t off = (uint32_t)((k0 + min(p * 32 + wave * 8 + sub, kn - 1)) * 64 + dc) * sizeof(T);
+    kr[p].load(kb, off);
+    vr[p].load(vb, off);
   }
-  if (tid < 64) {
-    const int c = h * 64 + tid;
-    float v = qp_bias[c];
-    for (int sp = 0; sp < qp_splits; ++sp) v += qp[((int64_t)sp * D + row) * d + c];
-    qs[tid] = v * 0.125f;
-  }
+  if (tid < 64) qs[tid] = q[(int64_t)row * d + h * 64 + tid] * 0.125f;
   __syncthreads();
   float qv[8];
 #pragma unroll
@@ -768,18 +608,16 @@ __global__ __launch_bounds__(256) void k_dattn_cross_bf16(const float* __restric
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     float kv[8];
-    load8((const bf16_t*)&kr[p], kv);
+    kr[p].get(kv);
     float a = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) a = fmaf(qv[i], kv[i], a);
-    a += __shfl_xor(a, 1, 64);
-    a += __shfl_xor(a, 2, 64);
-    a += __shfl_xor(a, 4, 64);
+    a = group8_sum_lanes(a);
     const int kk = p * 32 + wave * 8 + sub;
     sc[p] = kk < kn ? a : -INFINITY;
     mx = fmaxf(mx, sc[p]);
   }
-  mx = wave_max(mx);
+  mx = stride8_max_lanes(mx);
   if (lane == 0) red[0][wave] = mx;
   __syncthreads();
   const float M = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
@@ -793,20 +631,14 @@ __global__ __launch_bounds__(256) void k_dattn_cross_bf16(const float* __restric
     const float pr = expf(sc[p] - M);                // 0 for keys past the chunk
     l += pr;
     float vv[8];
-    load8((const bf16_t*)&vr[p], vv);
+    vr[p].keep(p * 32 + wave * 8 + sub < kn);
+    vr[p].get(vv);
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = fmaf(pr, vv[i], acc[i]);
   }
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    float a = acc[i];
-    a += __shfl_xor(a, 8, 64);
-    a += __shfl_xor(a, 16, 64);
-    a += __shfl_xor(a, 32, 64);
-    acc[i] = a;
-  }
-  // each key's probability was added by its 8 lanes
-  l = wave_sum(l) * 0.125f;
+  for (int i = 0; i < 8; ++i) acc[i] = stride8_sum_lanes(acc[i]);
+  l = stride8_sum_lanes(l);                          // (a key's eight lanes hold the same)
   if (lane < 8) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) ored[wave][dc + i] = acc[i];
@@ -814,7 +646,7 @@ __global__ __launch_bounds__(256) void k_dattn_cross_bf16(const float* __restric
   if (lane == 0) red[1][wave] = l;
   __syncthreads();
   if (tid < 64) {
-    float* rec = part + (((int64_t)row * n_head + h) * DA_NCH + chunk) * DA_REC;
+    float* rec = part + (((int64_t)row * n_head + h) * NCH + chunk) * DA_REC;
     rec[2 + tid] = ored[0][tid] + ored[1][tid] + ored[2][tid] + ored[3][tid];
     if (tid == 0) {
       rec[0] = M;
@@ -823,75 +655,67 @@ __global__ __launch_bounds__(256) void k_dattn_cross_bf16(const float* __restric
   }
 }
 
-// bf16 decode self attention: one block per (row, head) over the row's
-// position + 1 keys, writing the output directly.  The keys go in two halves
-// of DS_NP passes (224 keys) each, so a thread holds only one half's K and V
-// rows (about 90 VGPRs: five blocks per CU, which is what the short rows'
-// latency needs); the second half, present only for rows longer than 224
-// keys, loads its keys as soon as the first half's scores are done and its
-// values once the first half's weighted sum is, and joins through the usual
-// online-softmax rescale (block-wide maxima, so all lanes share one
-// reference).  The query, key and value of the step are bias + the
-// qp_splits float32 partial sums of the QKV product (qp[s][row][3d]); the new
-// key and value, rounded to bf16, go into the cache at the last position and
-// into the scores from LDS.
-constexpr int DS_NP = 7;
-constexpr int DS_HALF = DS_NP * 32;
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_dattn_self_bf16(const float* __restrict__ qp, int qp_splits,
-                                                         const float* __restrict__ qp_bias, int D,
-                                                         bf16_t* cache, int64_t slot_stride,
-                                                         int64_t layer_off, const int32_t* slots,
-                                                         const int32_t* pos, int n_head,
-                                                         bf16_t* __restrict__ out) {
-  static_assert(2 * DS_HALF >= kTextCtx, "two halves cover the decoder context");
-  __shared__ float qs[64];
-  __shared__ __attribute__((aligned(16))) bf16_t kvnew[2][64];
-  __shared__ float red[3][4];
+// One wave per (row, head).
+template <typename T>
+__global__ __launch_bounds__(256) void k_cross_merge(const float* __restrict__ part, int n,
+                                                     T* __restrict__ out) {
+  const int w = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (w < n) St<T>::st(out, (int64_t)w * kHeadDim + lane, cross_merge<T>(part, w, lane));
+}
+
+// Decode self attention: one block per (row, head) over the row's position + 1
+// keys, writing the output directly.  The keys go in parts of 32 NP, so a
+// thread holds only one part's K and V rows (bf16: two parts of 224 keys, about
+// 90 VGPRs, five blocks per CU, which is what the short rows' latency needs);
+// a further part, present only for rows long enough, loads its keys as soon as
+// the part before has its scores and its values once that part's weighted sum
+// is done, and joins through the usual online-softmax rescale (block-wide
+// maxima, so all lanes share one reference).  The step's query, key and value
+// are qkv [D][3d]; the new key and value, rounded to the storage type, go into
+// the cache at the last position and into the scores from LDS.
+template <typename T>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
+void k_dattn_self(const float* __restrict__ qkv, T* cache, int64_t slot_stride, int64_t layer_off,
+                  const int32_t* __restrict__ slots, const int32_t* __restrict__ pos, int n_head,
+                  T* __restrict__ out) {
+  constexpr int NP = sizeof(T) == 2 ? 5 : 3, PART = 32 * NP;
+  constexpr int NPART = (kTextCtx + PART - 1) / PART;
+  __shared__ __attribute__((aligned(16))) float qs[64];
+  __shared__ __attribute__((aligned(16))) T kvnew[2][64];
+  __shared__ float red[NPART + 1][4];
   __shared__ float ored[4][64];
   const int h = blockIdx.x, row = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int d = n_head * 64;
   const int n = pos[row] + 1;                       // keys, this step's included
-  const int slot = slots[row];
-  bf16_t* kb = cache + (int64_t)slot * slot_stride + layer_off + (int64_t)h * kTextCtx * 64;
-  bf16_t* vb = kb + (int64_t)n_head * kTextCtx * 64;
+  T* kb = cache + (int64_t)slots[row] * slot_stride + layer_off + (int64_t)h * kTextCtx * 64;
+  T* vb = kb + (int64_t)n_head * kTextCtx * 64;
   const int sub = lane >> 3, dc = (lane & 7) * 8;
-  const bool two = n > DS_HALF;                     // block-uniform
-  auto key_of = [&](int hf, int p) { return hf * DS_HALF + p * 32 + wave * 8 + sub; };
-
-  // cached keys (all but the last) of a half
-  uint4 kr[DS_NP], vr[DS_NP];
-  const uint4 zero = {0u, 0u, 0u, 0u};
-  auto load_k = [&](int hf) {
-#pragma unroll
-    for (int p = 0; p < DS_NP; ++p) {
-      const int key = key_of(hf, p);
-      kr[p] = zero;
-      if (key < n - 1) kr[p] = *(const uint4*)(kb + (int64_t)key * 64 + dc);
-    }
+  auto key_of = [&](int part, int p) { return part * PART + p * 32 + wave * 8 + sub; };
+  // cached keys (all but the last) of a part, without a branch: past them the
+  // last cached key again, not used
+  Row8<T> kr[NP], vr[NP];
+  const int last = max(n - 2, 0);
+  auto off_of = [&](int part, int p) {
+    return (uint32_t)(min(key_of(part, p), last) * 64 + dc) * (uint32_t)sizeof(T);
   };
-  auto load_v = [&](int hf) {
+  auto load_k = [&](int part) {
 #pragma unroll
-    for (int p = 0; p < DS_NP; ++p) {
-      const int key = key_of(hf, p);
-      vr[p] = zero;
-      if (key < n - 1) vr[p] = *(const uint4*)(vb + (int64_t)key * 64 + dc);
-    }
+    for (int p = 0; p < NP; ++p) kr[p].load(kb, off_of(part, p));
+  };
+  auto load_v = [&](int part) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) vr[p].load(vb, off_of(part, p));
   };
   load_k(0);
   load_v(0);
-  // query, new key and value: bias + the product's partials
-  if (tid < 192) {
-    const int part_i = tid >> 6, j = tid & 63;       // 0: q, 1: k, 2: v
-    const int c = part_i * d + h * 64 + j;
-    float v = qp_bias[c];
-    for (int sp = 0; sp < qp_splits; ++sp) v += qp[((int64_t)sp * D + row) * 3 * d + c];
-    if (part_i == 0) {
-      qs[j] = v * 0.125f;
+  if (wave < 3) {                                    // q, the new k, the new v
+    const float v = qkv[((int64_t)row * 3 + wave) * d + h * 64 + lane];
+    if (wave == 0) {
+      qs[lane] = v * 0.125f;
     } else {
-      const bf16_t b = f2bf(v);
-      kvnew[part_i - 1][j] = b;
-      (part_i == 1 ? kb : vb)[(int64_t)(n - 1) * 64 + j] = b;
+      St<T>::st(kvnew[wave - 1], lane, v);
+      St<T>::st(wave == 1 ? kb : vb, (int64_t)(n - 1) * 64 + lane, v);
     }
   }
   __syncthreads();
@@ -902,123 +726,96 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   float M = -INFINITY, l = 0.f, acc[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-  auto half = [&](int hf) {
 #pragma unroll
-    for (int p = 0; p < DS_NP; ++p)
-      if (key_of(hf, p) == n - 1) {
-        kr[p] = *(const uint4*)&kvnew[0][dc];
-        vr[p] = *(const uint4*)&kvnew[1][dc];
-      }
-    float sc[DS_NP];
+  for (int part = 0; part < NPART; ++part) {
+    if (part * PART >= n) break;                     // block-uniform
+    const bool more = (part + 1) * PART < n;
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      if (key_of(part, p) == n - 1) kr[p].load(&kvnew[0][dc], 0);
+    float sc[NP];
     float mx = -INFINITY;
 #pragma unroll
-    for (int p = 0; p < DS_NP; ++p) {
+    for (int p = 0; p < NP; ++p) {
       float kv[8];
-      load8((const bf16_t*)&kr[p], kv);
+      kr[p].get(kv);
       float a = 0.f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) a = fmaf(qv[i], kv[i], a);
-      a += __shfl_xor(a, 1, 64);
-      a += __shfl_xor(a, 2, 64);
-      a += __shfl_xor(a, 4, 64);
-      sc[p] = key_of(hf, p) < n ? a : -INFINITY;
+      a = group8_sum_lanes(a);
+      sc[p] = key_of(part, p) < n ? a : -INFINITY;
       mx = fmaxf(mx, sc[p]);
     }
-    mx = wave_max(mx);
-    if (lane == 0) red[hf][wave] = mx;
+    mx = stride8_max_lanes(mx);
+    if (lane == 0) red[part][wave] = mx;
     __syncthreads();
-    if (hf == 0 && two) load_k(1);                   // the first half's keys are done with
-    const float Mn = fmaxf(M, fmaxf(fmaxf(red[hf][0], red[hf][1]), fmaxf(red[hf][2], red[hf][3])));
-    const float f = expf(M - Mn);                    // 0 on the first half (M = -inf)
+    if (more) load_k(part + 1);                      // this part's keys are done with
+    const float Mn =
+        fmaxf(M, fmaxf(fmaxf(red[part][0], red[part][1]), fmaxf(red[part][2], red[part][3])));
+    const float f = expf(M - Mn);                    // 0 on the first part (M = -inf)
     l *= f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] *= f;
 #pragma unroll
-    for (int p = 0; p < DS_NP; ++p) {
+    for (int p = 0; p < NP; ++p) {
       const float pr = expf(sc[p] - Mn);             // 0 for keys past the row
       l += pr;
       float vv[8];
-      load8((const bf16_t*)&vr[p], vv);
+      vr[p].keep(key_of(part, p) < n);
+      if (key_of(part, p) == n - 1) vr[p].load(&kvnew[1][dc], 0);
+      vr[p].get(vv);
 #pragma unroll
       for (int i = 0; i < 8; ++i) acc[i] = fmaf(pr, vv[i], acc[i]);
     }
     M = Mn;
-    if (hf == 0 && two) load_v(1);                   // ... and so are its values
-  };
-  half(0);
-  if (two) half(1);
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    float a = acc[i];
-    a += __shfl_xor(a, 8, 64);
-    a += __shfl_xor(a, 16, 64);
-    a += __shfl_xor(a, 32, 64);
-    acc[i] = a;
+    if (more) load_v(part + 1);                      // ... and so are its values
   }
-  // each key's probability was added by its 8 lanes
-  l = wave_sum(l) * 0.125f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i] = stride8_sum_lanes(acc[i]);
+  l = stride8_sum_lanes(l);                          // (a key's eight lanes hold the same)
   if (lane < 8) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) ored[wave][dc + i] = acc[i];
   }
-  if (lane == 0) red[2][wave] = l;
+  if (lane == 0) red[NPART][wave] = l;
   __syncthreads();
   if (tid < 64) {
     const float o = ored[0][tid] + ored[1][tid] + ored[2][tid] + ored[3][tid];
-    const float L = red[2][0] + red[2][1] + red[2][2] + red[2][3];
-    out[(int64_t)row * d + h * 64 + tid] = f2bf(o / L);
+    const float L = red[NPART][0] + red[NPART][1] + red[NPART][2] + red[NPART][3];
+    St<T>::st(out, (int64_t)row * d + h * 64 + tid, o / L);
   }
 }
 
-int decode_attn_part_floats(int D, int n_head) { return D * n_head * DA_NCH * DA_REC; }
+int decode_attn_part_floats(int D, int n_head) { return D * n_head * kCrossChunks<float> * DA_REC; }
 
 template <typename T>
-void decode_self_attn(const T* qkv, const float* qkv_part, int qkv_splits, const float* qkv_bias,
-                      T* cache, int64_t slot_stride, int64_t layer_off, const int32_t* slots,
-                      const int32_t* pos, int D, int n_head, T* out, float* part,
+void decode_self_attn(const float* qkv, T* cache, int64_t slot_stride, int64_t layer_off,
+                      const int32_t* slots, const int32_t* pos, int D, int n_head, T* out,
                       hipStream_t s) {
-  if (D <= 0) return;
-  if constexpr (sizeof(T) == 2) {
-    k_dattn_self_bf16<<<dim3(n_head, D, 1), 256, 0, s>>>(
-        qkv_part, qkv_splits, qkv_bias, D, (bf16_t*)cache, slot_stride, layer_off, slots, pos,
-        n_head, (bf16_t*)out);
-    return;
-  }
-  constexpr int nch = (kTextCtx + DA_CK - 1) / DA_CK;
-  k_decode_attn<T, true><<<dim3(n_head, D, nch), 256, 0, s>>>(
-      qkv, nullptr, 0, nullptr, D, cache, slot_stride, layer_off, slots, pos, n_head, part);
-  k_decode_combine<T, true><<<(D * n_head + 3) / 4, 256, 0, s>>>(part, pos, D, n_head, out);
+  if (D > 0)
+    k_dattn_self<T><<<dim3(n_head, D), 256, 0, s>>>(qkv, cache, slot_stride,
+                                                    layer_off, slots, pos, n_head, out);
 }
 template <typename T>
-void decode_cross_attn(const float* q_part, int q_splits, const float* q_bias, T* cache,
-                       int64_t slot_stride, int64_t layer_off, const int32_t* slots, int D,
-                       int n_head, T* out, float* part, hipStream_t s) {
-  if (D <= 0) return;
-  constexpr int nch = (kCtx + DA_CK - 1) / DA_CK;
-  if constexpr (sizeof(T) == 2) {
-    static_assert(DA_CK % 32 == 0, "passes");
-    k_dattn_cross_bf16<DA_CK / 32><<<dim3(n_head, D, nch), 256, 0, s>>>(
-        q_part, q_splits, q_bias, D, (const bf16_t*)cache, slot_stride, layer_off, slots, n_head,
-        part);
-    k_decode_combine<T, false><<<(D * n_head + 3) / 4, 256, 0, s>>>(part, nullptr, D, n_head, out);
-    return;
-  }
-  k_decode_attn<T, false><<<dim3(n_head, D, nch), 256, 0, s>>>(
-      nullptr, q_part, q_splits, q_bias, D, cache, slot_stride, layer_off, slots, nullptr, n_head,
-      part);
-  k_decode_combine<T, false><<<(D * n_head + 3) / 4, 256, 0, s>>>(part, nullptr, D, n_head, out);
+void decode_cross_attn(const float* q, const T* cache, int64_t slot_stride, int64_t layer_off,
+                       const int32_t* slots, int D, int n_head, float* part, hipStream_t s) {
+  if (D > 0)
+    k_dattn_cross<T><<<dim3(n_head, D, kCrossChunks<T>), 256, 0, s>>>(
+        q, cache, slot_stride, layer_off, slots, n_head, part);
 }
-template void decode_self_attn<float>(const float*, const float*, int, const float*, float*,
-                                      int64_t, int64_t, const int32_t*, const int32_t*, int, int,
-                                      float*, float*, hipStream_t);
-template void decode_self_attn<bf16_t>(const bf16_t*, const float*, int, const float*, bf16_t*,
-                                       int64_t, int64_t, const int32_t*, const int32_t*, int, int,
-                                       bf16_t*, float*, hipStream_t);
-template void decode_cross_attn<float>(const float*, int, const float*, float*, int64_t,
-                                       int64_t, const int32_t*, int, int, float*, float*,
-                                       hipStream_t);
-template void decode_cross_attn<bf16_t>(const float*, int, const float*, bf16_t*, int64_t,
-                                        int64_t, const int32_t*, int, int, bf16_t*, float*,
-                                        hipStream_t);
+template <typename T>
+void decode_cross_merge(const float* part, int D, int n_head, T* out, hipStream_t s) {
+  if (D > 0) k_cross_merge<T><<<(D * n_head + 3) / 4, 256, 0, s>>>(part, D * n_head, out);
+}
+template void decode_self_attn<float>(const float*, float*, int64_t, int64_t, const int32_t*,
+                                      const int32_t*, int, int, float*, hipStream_t);
+template void decode_self_attn<bf16_t>(const float*, bf16_t*, int64_t, int64_t, const int32_t*,
+                                       const int32_t*, int, int, bf16_t*, hipStream_t);
+template void decode_cross_attn<float>(const float*, const float*, int64_t, int64_t, const int32_t*,
+                                       int, int, float*, hipStream_t);
+template void decode_cross_attn<bf16_t>(const float*, const bf16_t*, int64_t, int64_t,
+                                        const int32_t*, int, int, float*, hipStream_t);
+template void decode_cross_merge<float>(const float*, int, int, float*, hipStream_t);
+template void decode_cross_merge<bf16_t>(const float*, int, int, bf16_t*, hipStream_t);
 
 }  // namespace asr

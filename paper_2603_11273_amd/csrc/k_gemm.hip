@@ -5,9 +5,6 @@
 //    (bias, exact GELU, fp32 residual add, conv-stem row mapping, scatter of
 //    all decoder layers' cross K/V into a slot's cache).
 //  * gemm_f32: the same contract on fp32 MFMA (the fp32 model path).
-//  * dgemm_bf16 / dgemm_f32: skinny products for the decode rows (weights
-//    streamed once): bias / GELU fused into one slice, or float32 partial
-//    sums of a few K slices that the next kernel adds up.
 //  * vocab_argmax_bf16: the tied vocabulary projection fused with a per-row
 //    argmax (lowest index on ties) over each 64-column tile, finished by a
 //    deterministic cross-tile reduction.
@@ -445,34 +442,6 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_bf16(AView a, const bf16_t
 // tile publishes it and frees the buffer the next tile is loaded into.
 // Requires K % BK == 0.
 // ---------------------------------------------------------------------------
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt");
-  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
-}
-
-template <int MAXN>
-__device__ __forceinline__ void wait_vmcnt_rt(int n) {
-  // n is wave-uniform; the immediate must be a constant
-  if constexpr (MAXN > 0) {
-    if (n >= MAXN) { wait_vmcnt<MAXN>(); return; }
-    wait_vmcnt_rt<MAXN - 1>(n);
-  } else {
-    wait_vmcnt<0>();
-  }
-}
-
-__device__ __forceinline__ void lds_dma16(uint32_t lds_addr, const void* gptr) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
-               :: "s"(lds_addr), "v"(gptr) : "memory", "m0");
-}
-// Same with a wave-uniform 64-bit base in SGPRs and a 32-bit per-lane byte
-// offset: no per-load address arithmetic in vector registers.
-__device__ __forceinline__ void lds_dma16_s(uint32_t lds_addr, uint32_t voff, const void* sbase) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(lds_addr), "v"(voff), "s"(sbase) : "memory", "m0");
-}
-
 template <int BM, int BN, int BK, int WM, int WN, int S, int KIND, int SCHED = 0>
 __global__ __launch_bounds__(WM* WN * 64) void k_gemm_bf16_dma(AView a,
                                                               const bf16_t* __restrict__ w,
@@ -1493,27 +1462,22 @@ void gemm_f32(const AView& a, const float* w, int M, int N, int K, const Epilogu
 }
 
 // ---------------------------------------------------------------------------
-// Decode GEMMs and the vocabulary projection (skinny products)
+// Vocabulary projection (a skinny product)
 // ---------------------------------------------------------------------------
-// A decode step multiplies at most 128 rows by each weight matrix once, so
-// the product streams the weights from HBM (128 flops per weight byte, far
-// below the MFMA ridge) and the rows ride along from L2.  A block owns a
-// strip of 32 WN weight rows (output columns) and all 128 row slots over a K
-// range, in 64-deep chunks: each chunk's weight tile and activation tile go
-// global -> LDS with global_load_lds_dwordx4, eight lanes per 128-byte row
-// segment (whole cache lines per instruction), with the round-robin XOR
-// swizzle of the encoder GEMM (16-byte slot c of row r holds chunk
-// c ^ ((r >> 1) & 7): conflict-free fragment reads).  The two operands have
-// rings of their own: the weights, which come cold from HBM, run NW chunks
-// ahead (most of a block's strip is in flight at once); the activations, an
-// L2 hit, run NX chunks ahead.  Wave w computes strip w % WN against 32 WN
-// activation rows with v_mfma_f32_32x32x16_bf16: weight rows are the "A"
-// operand, activation rows the "B" operand.
+// A decode step multiplies at most 128 rows by the token embedding once, so
+// the product streams the table from HBM (128 flops per byte, far below the
+// MFMA ridge) and the rows ride along from L2.  A block owns a strip of 32 WN
+// table rows and all 128 row slots, in 64-deep chunks of K: each chunk's table
+// tile and activation tile go global -> LDS with global_load_lds_dwordx4, eight
+// lanes per 128-byte row segment (whole cache lines per instruction), with the
+// round-robin XOR swizzle of the encoder GEMM (16-byte slot c of row r holds
+// chunk c ^ ((r >> 1) & 7): conflict-free fragment reads).  The two operands
+// have rings of their own, NW and NX chunks deep.  Wave w computes strip w % WN
+// against 32 WN activation rows with v_mfma_f32_32x32x16_bf16: table rows are
+// the "A" operand, activation rows the "B" operand.
 constexpr int SK_BK = 64;          // K per chunk
 
 __device__ __forceinline__ int sk_swz(int row) { return (row >> 1) & 7; }
-
-enum SkEpi : int32_t { SK_PARTIAL = 0, SK_BIAS = 1, SK_GELU = 2, SK_ARGMAX = 3 };
 
 // Larger key = larger value, then lower index.  Any NaN gets the largest
 // value key so that it always wins and the finishing pass reports it.
@@ -1523,10 +1487,8 @@ __device__ __forceinline__ uint64_t argmax_key(float v, int n) {
 }
 
 struct SkOut {
-  void* out;            // PARTIAL: float [splits][D][N]; BIAS/GELU: bf16 [D][N]
-  const float* bias;    // BIAS/GELU
-  uint64_t* keys;       // ARGMAX: [D][N / 32] best key per 32-row tile
-  float* logits;        // ARGMAX: optional float [D][N]
+  uint64_t* keys;       // [D][N / 32] best key per 32-row tile
+  float* logits;        // optional float [D][N]
 };
 
 // Loads issued after chunk c's activation tile (which follows every earlier
@@ -1546,10 +1508,10 @@ __device__ __forceinline__ int sk_after(int c, int nck, int lpw, int lpx) {
   return n;
 }
 
-template <int WN, int NW, int NX, int EPI>
+template <int WN, int NW, int NX>
 __global__ __launch_bounds__(256) void k_skinny_bf16(const bf16_t* __restrict__ x,
                                                      const bf16_t* __restrict__ w, int D, int N,
-                                                     int K, int KC, SkOut o) {
+                                                     int K, SkOut o) {
   constexpr int RB = WN;                         // row blocks of 32 per wave
   constexpr int WR = 32 * WN;                    // weight rows per block
   constexpr int WSTAGE = WR * SK_BK, XSTAGE = 128 * SK_BK;   // elements per ring stage
@@ -1561,8 +1523,7 @@ __global__ __launch_bounds__(256) void k_skinny_bf16(const bf16_t* __restrict__ 
   bf16_t* xring = smem + NW * WSTAGE;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l32 = lane & 31, lh = lane >> 5;
-  const int n0 = blockIdx.x * WR, split = blockIdx.y;
-  const int kb = split * KC, nck = KC / SK_BK;
+  const int n0 = blockIdx.x * WR, nck = K / SK_BK;
   const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) bf16_t*)smem);
   const uint32_t xlds0 = lds0 + (uint32_t)(NW * WSTAGE * 2);
   // DMA: instruction i of a wave fills rows 8 i .. 8 i + 7 of its share; lane
@@ -1573,14 +1534,14 @@ __global__ __launch_bounds__(256) void k_skinny_bf16(const bf16_t* __restrict__ 
     const int row = wave * 32 + i * 8;                               // activation rows
     xdst[i] = __builtin_amdgcn_readfirstlane(xlds0 + (uint32_t)(row * SK_BK * 2));
     const int r = row + (lane >> 3);
-    xoff[i] = (uint32_t)(((int64_t)min(r, D - 1) * K + kb + (((lane & 7) ^ sk_swz(r)) * 8)) * 2);
+    xoff[i] = (uint32_t)(((int64_t)min(r, D - 1) * K + (((lane & 7) ^ sk_swz(r)) * 8)) * 2);
   }
 #pragma unroll
   for (int i = 0; i < WN; ++i) {
     const int row = wave * 8 * WN + i * 8;                           // weight rows
     wdst[i] = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(row * SK_BK * 2));
     const int r = row + (lane >> 3);
-    woff[i] = (uint32_t)(((int64_t)min(n0 + r, N - 1) * K + kb + (((lane & 7) ^ sk_swz(r)) * 8)) * 2);
+    woff[i] = (uint32_t)(((int64_t)min(n0 + r, N - 1) * K + (((lane & 7) ^ sk_swz(r)) * 8)) * 2);
   }
   auto issue_w = [&](int c) {
     const uint32_t so = (uint32_t)((c % NW) * WSTAGE * 2);
@@ -1641,222 +1602,39 @@ __global__ __launch_bounds__(256) void k_skinny_bf16(const bf16_t* __restrict__ 
 #pragma unroll
   for (int j = 0; j < RB; ++j) {
     const int row = xrow[j];
-    if constexpr (EPI == SK_ARGMAX) {
-      uint64_t best = 0;
+    uint64_t best = 0;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int n = nb + (r >> 2) * 8 + lh * 4 + (r & 3);
-        if (n < N) {
-          const uint64_t kk = argmax_key(acc[j][r], n);
-          best = kk > best ? kk : best;
-          if (o.logits && row < D) o.logits[(int64_t)row * N + n] = acc[j][r];
-        }
-      }
-      const uint32_t plo = __shfl_xor((uint32_t)best, 32, 64);
-      const uint32_t phi = __shfl_xor((uint32_t)(best >> 32), 32, 64);
-      const uint64_t other = ((uint64_t)phi << 32) | plo;
-      best = other > best ? other : best;
-      const int n_tiles = (N + 31) / 32;
-      if (lane < 32 && row < D && nb < N) o.keys[(int64_t)row * n_tiles + nb / 32] = best;
-    } else {
-      if (row >= D) continue;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int n = nb + g * 8 + lh * 4;
-        float4 v = make_float4(acc[j][g * 4], acc[j][g * 4 + 1], acc[j][g * 4 + 2],
-                               acc[j][g * 4 + 3]);
-        if constexpr (EPI == SK_PARTIAL) {
-          *(float4*)((float*)o.out + ((int64_t)split * D + row) * N + n) = v;
-        } else {
-          v = add4(v, *(const float4*)(o.bias + n));
-          if constexpr (EPI == SK_GELU) v = gelu4(v);
-          typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-          u32x2 u;
-          u.x = pack2_bf16(v.x, v.y);
-          u.y = pack2_bf16(v.z, v.w);
-          *(u32x2*)((bf16_t*)o.out + (int64_t)row * N + n) = u;
-        }
+    for (int r = 0; r < 16; ++r) {
+      const int n = nb + (r >> 2) * 8 + lh * 4 + (r & 3);
+      if (n < N) {
+        const uint64_t kk = argmax_key(acc[j][r], n);
+        best = kk > best ? kk : best;
+        if (o.logits && row < D) o.logits[(int64_t)row * N + n] = acc[j][r];
       }
     }
+    const uint32_t plo = __shfl_xor((uint32_t)best, 32, 64);
+    const uint32_t phi = __shfl_xor((uint32_t)(best >> 32), 32, 64);
+    const uint64_t other = ((uint64_t)phi << 32) | plo;
+    best = other > best ? other : best;
+    const int n_tiles = (N + 31) / 32;
+    if (lane < 32 && row < D && nb < N) o.keys[(int64_t)row * n_tiles + nb / 32] = best;
   }
 }
 
-template <int WN, int NW, int NX, int EPI>
-static void launch_skinny(const bf16_t* x, const bf16_t* w, int D, int N, int K, int splits,
-                          const SkOut& o, hipStream_t s) {
+template <int WN, int NW, int NX>
+static void launch_skinny(const bf16_t* x, const bf16_t* w, int D, int N, int K, const SkOut& o,
+                          hipStream_t s) {
   constexpr size_t lds = ((size_t)NW * 32 * WN + (size_t)NX * 128) * SK_BK * sizeof(bf16_t);
   static_assert(lds <= 160 * 1024, "LDS");
-  auto kfn = k_skinny_bf16<WN, NW, NX, EPI>;
+  auto kfn = k_skinny_bf16<WN, NW, NX>;
   static bool attr = false;
   if (!attr) {
     (void)hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
     attr = true;
   }
-  dim3 grid((N + 32 * WN - 1) / (32 * WN), splits);
-  kfn<<<grid, 256, lds, s>>>(x, w, D, N, K, K / splits, o);
+  kfn<<<(N + 32 * WN - 1) / (32 * WN), 256, lds, s>>>(x, w, D, N, K, o);
 }
-
-// K slices of a partial-sum product: the largest divisor of K / 64 that keeps
-// the grid (N / 32 strips x slices) within one block per CU, at most 16.
-int dgemm_splits(int N, int K) {
-  const int tiles = N / 32, q = K / 64;
-  int best = 1;
-  for (int sp = 1; sp <= 16 && sp <= q; ++sp)
-    if (q % sp == 0 && tiles * sp <= 256) best = sp;
-  return best;
-}
-
-int dgemm_bf16(const bf16_t* x, const bf16_t* w, int D, int N, int K, int epi,
-               const float* bias, void* out, hipStream_t s) {
-  // N % 32 == 0, K % 64 == 0 and D <= 128 are checked when the context is created
-  if (D <= 0) return 1;
-  SkOut o{out, bias, nullptr, nullptr};
-  // weight ring 16 x 4 KB (15 chunks in flight), activation ring 3 x 16 KB
-  if (epi == DG_PARTIAL) {
-    const int sp = dgemm_splits(N, K);
-    launch_skinny<1, 16, 3, SK_PARTIAL>(x, w, D, N, K, sp, o, s);
-    return sp;
-  }
-  if (epi == DG_GELU)
-    launch_skinny<1, 16, 3, SK_GELU>(x, w, D, N, K, 1, o, s);
-  else
-    launch_skinny<1, 16, 3, SK_BIAS>(x, w, D, N, K, 1, o, s);
-  return 1;
-}
-
-void dgemm_f32(const float* x, const float* w, int D, int N, int K, float* out, hipStream_t s) {
-  AView a{x, K, 0, 1 << 30};
-  Epilogue e{};
-  e.kind = EPI_STORE;
-  e.out = out;
-  e.ldc = N;
-  gemm_f32(a, w, D, N, K, e, s);
-}
-
-template <typename T>
-__global__ void k_dgemm_reduce(const float* partial, int splits, int D, int N,
-                               const float* bias, int mode, void* out) {
-  int64_t n_all = (int64_t)D * N;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_all;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    int n = (int)(i % N);
-    float v = bias ? bias[n] : 0.f;
-    for (int s = 0; s < splits; ++s) v += partial[(int64_t)s * n_all + i];
-    if (mode == 0) {
-      St<T>::st((T*)out, i, v);
-    } else if (mode == 1) {
-      St<T>::st((T*)out, i, gelu_erf(v));
-    } else {
-      ((float*)out)[i] += v;
-    }
-  }
-}
-template <typename T>
-void dgemm_reduce(const float* partial, int splits, int D, int N, const float* bias, int mode,
-                  void* out, hipStream_t s) {
-  int64_t n = (int64_t)D * N;
-  if (n <= 0) return;
-  int g = (int)((n + 255) / 256);
-  if (g > 8192) g = 8192;
-  k_dgemm_reduce<T><<<g, 256, 0, s>>>(partial, splits, D, N, bias, mode, out);
-}
-template void dgemm_reduce<float>(const float*, int, int, int, const float*, int, void*,
-                                  hipStream_t);
-template void dgemm_reduce<bf16_t>(const float*, int, int, int, const float*, int, void*,
-                                   hipStream_t);
-
-// Split-K reduce fused with the residual add and the next LayerNorm: one
-// block per decode row.  Thread t sums the float4 column group t % G (G =
-// d/4) over the splits s = t / G, t / G + SG, ... (SG split groups, unrolled
-// so that several loads are in flight), the SG partial sums meet in LDS, and
-// the G owners finish the row:  h[b] += bias + sum_s partial[s][b];
-// xn[b] = LN(h[b]) (eps 1e-5).
-template <typename T>
-__global__ __launch_bounds__(1024) void k_reduce_resid_ln(const float* __restrict__ partial,
-                                                          int splits, int D, int d,
-                                                          const float* __restrict__ bias,
-                                                          float* __restrict__ h,
-                                                          const float* __restrict__ g,
-                                                          const float* __restrict__ beta, T* xn) {
-  __shared__ float4 part[1024];
-  __shared__ float red[2][16];
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int G = d >> 2, SG = blockDim.x / G;
-  const int grp = tid % G, sg = tid / G;
-  const int64_t rs = (int64_t)D * d;                 // stride between splits
-  const float* src = partial + (int64_t)b * d + grp * 4;
-  // the owners' row, bias and LayerNorm parameters load beside the partials
-  // (one memory round trip for the whole kernel)
-  float4 hv = make_float4(0.f, 0.f, 0.f, 0.f), bv = hv, gg = hv, bb = hv;
-  float* hp = h + (int64_t)b * d + tid * 4;
-  if (tid < G) {
-    hv = *(const float4*)hp;
-    bv = *(const float4*)(bias + tid * 4);
-    gg = *(const float4*)(g + tid * 4);
-    bb = *(const float4*)(beta + tid * 4);
-  }
-  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (sg < SG) {
-    int s = sg;
-    for (; s + 3 * SG < splits; s += 4 * SG) {
-      const float4 v0 = *(const float4*)(src + s * rs);
-      const float4 v1 = *(const float4*)(src + (s + SG) * rs);
-      const float4 v2 = *(const float4*)(src + (s + 2 * SG) * rs);
-      const float4 v3 = *(const float4*)(src + (s + 3 * SG) * rs);
-      a = add4(a, add4(add4(v0, v1), add4(v2, v3)));
-    }
-    for (; s < splits; s += SG) a = add4(a, *(const float4*)(src + s * rs));
-  }
-  part[tid] = a;
-  __syncthreads();
-  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-  float sum = 0.f;
-  if (tid < G) {
-    for (int k = 1; k < SG; ++k) a = add4(a, part[tid + k * G]);
-    v = add4(add4(hv, bv), a);
-    *(float4*)hp = v;
-    sum = (v.x + v.y) + (v.z + v.w);
-  }
-  const int nw = (blockDim.x + 63) >> 6;
-  sum = wave_sum(sum);
-  if (lane == 0) red[0][wave] = sum;
-  __syncthreads();
-  float tot = 0.f;
-  for (int w2 = 0; w2 < nw; ++w2) tot += red[0][w2];
-  const float mean = tot / d;
-  float q = 0.f;
-  if (tid < G) {
-    const float4 c = make_float4(v.x - mean, v.y - mean, v.z - mean, v.w - mean);
-    q = (c.x * c.x + c.y * c.y) + (c.z * c.z + c.w * c.w);
-  }
-  q = wave_sum(q);
-  if (lane == 0) red[1][wave] = q;
-  __syncthreads();
-  float var = 0.f;
-  for (int w2 = 0; w2 < nw; ++w2) var += red[1][w2];
-  const float rstd = rsqrtf(var / d + 1e-5f);
-  if (tid < G) {
-    const float o[4] = {(v.x - mean) * rstd * gg.x + bb.x, (v.y - mean) * rstd * gg.y + bb.y,
-                        (v.z - mean) * rstd * gg.z + bb.z, (v.w - mean) * rstd * gg.w + bb.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) St<T>::st(xn, (int64_t)b * d + tid * 4 + k, o[k]);
-  }
-}
-
-template <typename T>
-void reduce_resid_ln(const float* partial, int splits, int D, int d, const float* bias, float* h,
-                     const float* g, const float* beta, T* xn, hipStream_t s) {
-  if (D <= 0) return;
-  const int G = d / 4;                                // d % 64 == 0, d <= 2048
-  const int SG = std::max(1, 1024 / G);
-  const int threads = (G * SG + 63) / 64 * 64;
-  k_reduce_resid_ln<T><<<D, threads, 0, s>>>(partial, splits, D, d, bias, h, g, beta, xn);
-}
-template void reduce_resid_ln<float>(const float*, int, int, int, const float*, float*,
-                                     const float*, const float*, float*, hipStream_t);
-template void reduce_resid_ln<bf16_t>(const float*, int, int, int, const float*, float*,
-                                      const float*, const float*, bf16_t*, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Vocabulary projection + argmax
@@ -1871,12 +1649,12 @@ void vocab_argmax_bf16(const bf16_t* x, const bf16_t* emb, int D, int V, int K, 
                        int n_tiles, float* logits, hipStream_t s) {
   if (D <= 0) return;
   (void)n_tiles;   // = vocab_tiles(V): the kernel derives it from V
-  SkOut o{nullptr, nullptr, keys, logits};
+  SkOut o{keys, logits};
   // 128 vocabulary rows per block with a 3-chunk weight and 2-chunk
   // activation ring (80 KB of LDS): two blocks per CU, so the 406 blocks of
   // the 51866-row table are all resident at once instead of running in a
   // full round and a partial one
-  launch_skinny<4, 3, 2, SK_ARGMAX>(x, emb, D, V, K, 1, o, s);
+  launch_skinny<4, 3, 2>(x, emb, D, V, K, o, s);
 }
 
 void vocab_logits_f32(const float* x, const float* emb, int D, int V, int K, float* logits,

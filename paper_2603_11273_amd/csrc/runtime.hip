@@ -86,7 +86,7 @@ struct Layout {
          h1 = 0, x = 0, xn = 0, qkv = 0, vt = 0, att = 0, hid = 0, p_slots = 0;
   size_t vt_bytes = 0;
   size_t d_slots = 0, d_tokens = 0, d_pos = 0, d_h = 0, d_xn = 0, d_qkv = 0, d_att = 0,
-         d_hid = 0, d_partial = 0, d_apart = 0, d_logits = 0, d_keys = 0, d_argmax = 0,
+         d_hid = 0, d_part = 0, d_apart = 0, d_logits = 0, d_keys = 0, d_argmax = 0,
          d_flag = 0;
   size_t wstage = 0;
   int64_t wstage_floats = 0;
@@ -307,27 +307,15 @@ void plan(asr_ctx* c) {
   L.p_slots = b.take(P * 4);
   // decode scratch
   const int64_t D = std::max(1, g.max_decode);
-  const int64_t Nmax = std::max<int64_t>(3 * d, F);
   L.d_slots = b.take(D * 4);
   L.d_tokens = b.take(D * 4);
   L.d_pos = b.take(D * 4);
   L.d_h = b.take(D * d * f4);
-  L.d_xn = b.take(D * std::max<int64_t>(d, F) * es);
-  L.d_qkv = b.take(D * 3 * d * es);
+  L.d_xn = b.take(D * d * es);
+  L.d_qkv = b.take(D * 3 * d * f4);
   L.d_att = b.take(D * d * es);
   L.d_hid = b.take(D * F * es);
-  // partial sums of the decode products: the bf16 path splits the K range of
-  // the products whose output feeds a residual LayerNorm or the cross
-  // attention (N = d); the fp32 path holds one slice of any product
-  {
-    int64_t most = D * std::max<int64_t>(3 * d, F);
-    if (c->cfg.dtype == ASR_BF16)
-      most = std::max<int64_t>(
-          most, std::max<int64_t>(D * d * std::max(dgemm_splits((int)d, (int)d),
-                                                   dgemm_splits((int)d, (int)F)),
-                                  D * 3 * d * dgemm_splits((int)(3 * d), (int)d)));
-    L.d_partial = b.take(most * f4);
-  }
+  L.d_part = b.take(rows_part_floats((int)D, (int)d) * f4);
   L.d_apart = b.take((int64_t)decode_attn_part_floats((int)D, g.n_head) * f4);
   L.d_logits = b.take(D * (int64_t)std::max(1, g.vocab) * f4);
   L.d_keys = b.take(D * (int64_t)vocab_tiles(std::max(1, g.vocab)) * 8);
@@ -808,52 +796,17 @@ asr_status cross_kv(asr_ctx* c, const void* E, int n, int slot0) {
 // ---------------------------------------------------------------------------
 // Decode pipeline (rows already uploaded to d_slots / d_tokens / d_pos)
 // ---------------------------------------------------------------------------
-// Decode product with its epilogue: out = (GELU)(x W^T + bias) in the
-// storage type.  bf16: one kernel; fp32: the product, then the epilogue.
-template <typename T>
-void dgemm_out(asr_ctx* c, const T* x, size_t w_off, int D, int N, int K, size_t bias_off,
-               bool gelu, T* out) {
-  float* part = c->at<float>(c->L.d_partial);
-  const double bytes = (double)N * K * c->es + (double)D * K * c->es + (double)D * N * c->es;
-  timed(c, ASR_K_DGEMM, 2.0 * D * N * K, bytes, [&] {
-    if (c->bf16()) {
-      dgemm_bf16((const bf16_t*)x, c->at<bf16_t>(w_off), D, N, K, gelu ? DG_GELU : DG_BIAS,
-                 c->at<float>(bias_off), out, c->stream);
-    } else {
-      dgemm_f32((const float*)x, c->at<float>(w_off), D, N, K, part, c->stream);
-      dgemm_reduce<T>(part, 1, D, N, c->at<float>(bias_off), gelu ? 1 : 0, out, c->stream);
-    }
-  });
-}
+// A decode product (rows_*), timed with the traffic it cannot do without:
+// weights, operand and result once.
+// Rows up to which every block of a product repeats the preparation of its
+// rows: eight LayerNorms go to eight waves at once (one row at d = 1280: 4.5 us
+// for the cross query's product with it, 3.5 + 3.4 us apart); merging four
+// rows' records reads 84 KB a block.
+constexpr int kNormRows = 8, kMergeRows = 4;
 
-// Decode product left as float32 partial sums over K slices in d_partial
-// (the consumer adds the slices and the bias); returns the slice count.
-template <typename T>
-int dgemm_part(asr_ctx* c, const T* x, size_t w_off, int D, int N, int K) {
-  float* part = c->at<float>(c->L.d_partial);
-  int splits = 1;
-  const double bytes = (double)N * K * c->es + (double)D * K * c->es + (double)D * N * c->es;
-  timed(c, ASR_K_DGEMM, 2.0 * D * N * K, bytes, [&] {
-    if (c->bf16())
-      splits = dgemm_bf16((const bf16_t*)x, c->at<bf16_t>(w_off), D, N, K, DG_PARTIAL, nullptr,
-                          part, c->stream);
-    else
-      dgemm_f32((const float*)x, c->at<float>(w_off), D, N, K, part, c->stream);
-  });
-  return splits;
-}
-
-// Residual product (N = d): h += bias + x W^T, then xn = LayerNorm(h) with
-// (g, b) -- the product's K slices are added by the LayerNorm kernel.
-template <typename T>
-void dgemm_resid_ln(asr_ctx* c, const T* x, size_t w_off, int D, int K, size_t bias_off,
-                    float* h, size_t g_off, size_t b_off, T* xn) {
-  const int d = c->cfg.d_model;
-  const int splits = dgemm_part<T>(c, x, w_off, D, d, K);
-  timed(c, ASR_K_LN, 9.0 * D * d, (double)D * d * (4.0 * splits + 8 + c->es), [&] {
-    reduce_resid_ln<T>(c->at<float>(c->L.d_partial), splits, D, d, c->at<float>(bias_off), h,
-                       c->at<float>(g_off), c->at<float>(b_off), xn, c->stream);
-  });
+template <typename T, class F>
+void drows(asr_ctx* c, int D, int N, int K, double xy_bytes, F&& f) {
+  timed(c, ASR_K_DGEMM, 2.0 * D * N * K, (double)N * K * c->es + xy_bytes, f);
 }
 
 template <typename T>
@@ -861,53 +814,92 @@ asr_status decode_rows(asr_ctx* c, int D, const std::vector<int32_t>& pos_host, 
   const asr_model_cfg& g = c->cfg;
   const int d = g.d_model, F = g.d_ffn, H = g.n_head, V = g.vocab;
   const Layout& L = c->L;
+  hipStream_t s = c->stream;
   float* h = c->at<float>(L.d_h);
   T* xn = c->at<T>(L.d_xn);
-  T* qkv = c->at<T>(L.d_qkv);
+  float* qkv = c->at<float>(L.d_qkv);               // also the cross queries
   T* att = c->at<T>(L.d_att);
   T* hid = c->at<T>(L.d_hid);
+  float* rec = c->at<float>(L.d_apart);
   const int32_t* slots = c->at<int32_t>(L.d_slots);
   const int32_t* pos = c->at<int32_t>(L.d_pos);
   T* self_cache = c->at<T>(L.self_kv);
   T* cross_cache = c->at<T>(L.cross_kv);
   double self_keys = 0;
   for (int i = 0; i < D; ++i) self_keys += pos_host[i] + 1;
+  const double Dd = (double)D * d;
 
-  timed(c, ASR_K_OTHER, 0.0, (double)D * d * (c->es + 8), [&] {
+  timed(c, ASR_K_OTHER, 0.0, Dd * (c->es + 8), [&] {
     embed<T>(c->at<T>(L.tok_emb), c->at<float>(L.pos_emb), c->at<int32_t>(L.d_tokens), pos, D, d,
-             h, c->stream);
+             h, s);
   });
-  ln_any<T>(c, h, D, L.dec[0].ln1_g, L.dec[0].ln1_b, xn);
+  // Few rows run the LayerNorms at the start of the products that follow them
+  // (every block repeats them, which is shorter than a launch up to kNormRows
+  // rows), and up to kMergeRows the merge of the cross attention's records.
+  // Many bf16 rows split FC2's long K over blocks, and the kernel of the
+  // LayerNorm that follows adds the parts.  The sums are the same throughout.
+  const bool wide = c->bf16() && D > kFewRows;
+  bool normed = false;                                 // xn holds the LayerNorm of h
+  auto norm_product = [&](size_t lg, size_t lb, size_t wo, size_t bo, int N, bool gelu, void* out) {
+    if (D > kNormRows) {
+      if (!normed)
+        timed(c, ASR_K_LN, 8.0 * Dd, Dd * (4 + c->es), [&] {
+          rows_norm<T>(h, D, d, c->at<float>(lg), c->at<float>(lb), xn, s);
+        });
+      normed = false;
+      drows<T>(c, D, N, d, Dd * c->es + (double)D * N * (gelu ? c->es : 4), [&] {
+        rows_mem<T>(xn, c->at<T>(wo), c->at<float>(bo), D, N, d, gelu, out, s);
+      });
+    } else {
+      drows<T>(c, D, N, d, Dd * 4 + (double)D * N * (gelu ? c->es : 4), [&] {
+        rows_ln<T>(h, c->at<float>(lg), c->at<float>(lb), c->at<T>(wo), c->at<float>(bo), D, N, d,
+                   gelu, out, s);
+      });
+    }
+  };
+  auto resid_product = [&](const T* x, size_t wo, size_t bo) {
+    drows<T>(c, D, d, d, Dd * (8 + c->es), [&] {
+      rows_resid<T>(x, c->at<T>(wo), c->at<float>(bo), D, d, d, h, s);
+    });
+  };
   for (int l = 0; l < g.n_dec; ++l) {
     const DecLayer& w = L.dec[l];
-    // xn holds LN_attn(h) here; bf16: the QKV product stays in K-slice
-    // partial sums that the self-attention kernel adds up with the bias
-    int qkv_splits = 0;
-    if (c->bf16())
-      qkv_splits = dgemm_part<T>(c, xn, w.qkv_w, D, 3 * d, d);
-    else
-      dgemm_out<T>(c, xn, w.qkv_w, D, 3 * d, d, w.qkv_b, false, qkv);
+    norm_product(w.ln1_g, w.ln1_b, w.qkv_w, w.qkv_b, 3 * d, false, qkv);
     const int64_t self_off = (int64_t)l * 2 * H * kTextCtx * kHeadDim;
     timed(c, ASR_K_DATTN, 4.0 * self_keys * 64 * H, self_keys * 2 * 64 * H * c->es, [&] {
-      decode_self_attn<T>(qkv, c->at<float>(L.d_partial), qkv_splits, c->at<float>(w.qkv_b),
-                          self_cache, L.self_stride, self_off, slots, pos, D, H, att,
-                          c->at<float>(L.d_apart), c->stream);
+      decode_self_attn<T>(qkv, self_cache, L.self_stride, self_off, slots, pos, D, H, att, s);
     });
-    dgemm_resid_ln<T>(c, att, w.o_w, D, d, w.o_b, h, w.lnx_g, w.lnx_b, xn);
-    const int q_splits = dgemm_part<T>(c, xn, w.xq_w, D, d, d);
+    resid_product(att, w.o_w, w.o_b);
+    norm_product(w.lnx_g, w.lnx_b, w.xq_w, w.xq_b, d, false, qkv);
     const int64_t cross_off = (int64_t)l * 2 * H * kCtx * kHeadDim;
-    timed(c, ASR_K_DATTN, 4.0 * D * H * (double)kCtx * 64, (double)D * H * kCtx * 2 * 64 * c->es,
-          [&] {
-            decode_cross_attn<T>(c->at<float>(L.d_partial), q_splits, c->at<float>(w.xq_b),
-                                 cross_cache, L.cross_stride, cross_off, slots, D, H, att,
-                                 c->at<float>(L.d_apart), c->stream);
-          });
-    dgemm_resid_ln<T>(c, att, w.xo_w, D, d, w.xo_b, h, w.ln2_g, w.ln2_b, xn);
-    dgemm_out<T>(c, xn, w.fc1_w, D, F, d, w.fc1_b, true, hid);
-    // the last residual of the layer also produces the next LayerNorm input
+    timed(c, ASR_K_DATTN, 4.0 * Dd * kCtx, Dd * kCtx * 2 * c->es, [&] {
+      decode_cross_attn<T>(qkv, cross_cache, L.cross_stride, cross_off, slots, D, H, rec, s);
+    });
+    if (D <= kMergeRows) {
+      drows<T>(c, D, d, d, Dd * (c->es + 8), [&] {
+        rows_merge_resid<T>(rec, c->at<T>(w.xo_w), c->at<float>(w.xo_b), D, d, h, s);
+      });
+    } else {
+      timed(c, ASR_K_DATTN, 0.0, 0.0, [&] { decode_cross_merge<T>(rec, D, H, att, s); });
+      resid_product(att, w.xo_w, w.xo_b);
+    }
+    norm_product(w.ln2_g, w.ln2_b, w.fc1_w, w.fc1_b, F, true, hid);
     const bool last = l + 1 == g.n_dec;
-    dgemm_resid_ln<T>(c, hid, w.fc2_w, D, F, w.fc2_b, h, last ? L.lnf_g : L.dec[l + 1].ln1_g,
-                      last ? L.lnf_b : L.dec[l + 1].ln1_b, xn);
+    const float* ng = c->at<float>(last ? L.lnf_g : L.dec[l + 1].ln1_g);
+    const float* nb = c->at<float>(last ? L.lnf_b : L.dec[l + 1].ln1_b);
+    drows<T>(c, D, d, F, Dd * 8 + (double)D * F * c->es, [&] {
+      if constexpr (sizeof(T) == 2) {
+        if (wide) {
+          rows_resid_norm(hid, c->at<T>(w.fc2_w), c->at<float>(w.fc2_b), D, d, F, h, ng, nb, xn,
+                          c->at<float>(L.d_part), s);
+          normed = true;
+          return;
+        }
+      }
+      rows_resid<T>(hid, c->at<T>(w.fc2_w), c->at<float>(w.fc2_b), D, d, F, h, s);
+    });
+    if (last && !normed)
+      timed(c, ASR_K_LN, 8.0 * Dd, Dd * (4 + c->es), [&] { rows_norm<T>(h, D, d, ng, nb, xn, s); });
   }
   const int nt = vocab_tiles(V);
   int32_t* flag = c->at<int32_t>(L.d_flag);

@@ -1,0 +1,56 @@
+"""A decode row's logits do not depend on the rows beside it: the same rows,
+alone, in small batches and in batches past the 32 rows of a block (which take
+other block shapes, and the merge of the cross attention's key chunks in a
+kernel of its own), give the same bits, and the single rows match the oracle.
+The widths reach the products' limits: a K of fewer chunks than a block has
+waves, LDS too small for 32 prepared rows, an MLP that is not a power of two."""
+import numpy as np
+import pytest
+
+from oracle import whisper as OW
+from paper_2603_11273_amd import synth
+
+from gpu_util import TOL, cpu_params, make_context, needs_gpu, rel_err
+
+pytestmark = [pytest.mark.gpu, needs_gpu]
+
+
+@pytest.mark.parametrize("n_head,d_ffn,dtype,batches", [
+    (1, 64, "f32", [2, 5, 33]), (6, 1536, "f32", [3, 34, 128]), (20, 1344, "f32", [4, 17, 40]),
+    (2, 128, "bf16", [2, 31, 65]), (12, 3072, "bf16", [4, 5, 33, 128]),
+    (20, 5120, "bf16", [5, 40]), (32, 1920, "bf16", [5, 36]),
+])
+def test_rows_do_not_depend_on_the_batch(n_head, d_ffn, dtype, batches):
+    d = 64 * n_head
+    shape = synth.ModelShape("rows", 80, d, 0, 2, n_head, d_ffn, 500, dtype)
+    seed = 20260370 + n_head
+    B = max(batches)
+    ctx = make_context(shape, seed, max_slots=B, max_prefill=8, max_decode=B)
+    E = [synth.encoder_output(seed, b % 3, d).numpy() for b in range(B)]
+    kv = [synth.self_kv_prefix(seed, b, 2, n_head).numpy() for b in range(3)]
+    lengths = [(7 * b) % 440 for b in range(B)]
+    toks = synth.token_ids(seed, B, shape.vocab)
+    for b0 in range(0, B, 8):
+        part = list(range(b0, min(B, b0 + 8)))
+        ctx.debug_set_encoder_out(part, [-1] * len(part), [40] * len(part),
+                                  np.stack([E[b] for b in part]))
+
+    def step(rows):
+        for b in rows:
+            ctx.debug_set_self_kv(b, kv[b % 3], lengths[b])
+        return ctx.step(slots=rows, tokens=[int(toks[b]) for b in rows], want_logits=True)["logits"]
+
+    some = [0, 1, 2, 4]
+    alone = {b: step([b])[0] for b in some if b < B}
+    for n in batches:
+        got = step(list(range(n)))
+        for b in some:
+            if b < n:
+                assert np.array_equal(got[b], alone[b]), (n, b)
+    P = cpu_params(shape, seed)
+    for b in some[:2]:
+        ckv = OW.cross_kv(E[b], P, 2)
+        pre = kv[b % 3][:, :, :, :lengths[b]].transpose(0, 1, 3, 2, 4).reshape(2, 2, lengths[b], d)
+        st = OW.DecoderState(2, d, pre[:, 0], pre[:, 1])
+        ref = OW.decoder_step(int(toks[b]), st, ckv, P, 2, n_head)
+        assert rel_err(alone[b], ref) <= TOL[dtype]
