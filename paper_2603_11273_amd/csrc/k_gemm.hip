@@ -442,7 +442,7 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_bf16(AView a, const bf16_t
 // tile publishes it and frees the buffer the next tile is loaded into.
 // Requires K % BK == 0.
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int BK, int WM, int WN, int S, int KIND, int SCHED = 0>
+template <int BM, int BN, int BK, int WM, int WN, int S, int KIND>
 __global__ __launch_bounds__(WM* WN * 64) void k_gemm_bf16_dma(AView a,
                                                               const bf16_t* __restrict__ w,
                                                               int M, int N, int K, Epilogue e,
@@ -548,17 +548,6 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_bf16_dma(AView a,
 #pragma unroll
         for (int j = 0; j < FN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[p][i], bfr[p][j], acc[i][j], 0, 0, 0);
-      if constexpr (SCHED == 1) {
-        // interleave the next step's fragment reads with this step's MFMAs
-        if (kk + 1 < BK / 16) {
-#pragma unroll
-          for (int q = 0; q < FM + FN; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          }
-          __builtin_amdgcn_sched_group_barrier(0x008, FM * FN - (FM + FN), 0);
-        }
-      }
     }
   }
   wait_vmcnt<0>();
@@ -991,7 +980,6 @@ void k_gemm_bf16_ps(AView a,
   static_assert(FM + FN <= 15, "lgkmcnt");
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
   constexpr int STAGE = (BM + BN) * BK;
-  constexpr int kLgkmImm = 0xF | (0x3 << 14) | (0x7 << 4) | ((FM + FN) << 8);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WM, wn = wave / WM;
@@ -1036,16 +1024,25 @@ void k_gemm_bf16_ps(AView a,
     }
     src_tile = ti;
   };
-  auto issue = [&](int gi) {
+  // the direct loads of K tile gi, numbered 0 .. LPT - 1 (A's first): iss_begin
+  // sets the tile, iss(q) issues one
+  uint32_t iss_so = 0;
+  const bf16_t *iss_a = nullptr, *iss_b = nullptr;
+  auto iss_begin = [&](int gi) {
     const int ti = gi / nk, kt = gi - ti * nk;
     if (ti != src_tile) set_src(ti);
-    const uint32_t so = (uint32_t)((gi % S) * STAGE * 2);
-    const bf16_t* ak = abase + kt * BK;
-    const bf16_t* bk = w + kt * BK;
+    iss_so = (uint32_t)((gi % S) * STAGE * 2);
+    iss_a = abase + kt * BK;
+    iss_b = w + kt * BK;
+  };
+  auto iss = [&](int q) {
+    if (q < IA) lds_dma16_s(adst[q] + iss_so, aoff[q], iss_a);
+    else lds_dma16_s(bdst[q - IA] + iss_so, boff[q - IA], iss_b);
+  };
+  auto issue = [&](int gi) {
+    iss_begin(gi);
 #pragma unroll
-    for (int i = 0; i < IA; ++i) lds_dma16_s(adst[i] + so, aoff[i], ak);
-#pragma unroll
-    for (int i = 0; i < IB; ++i) lds_dma16_s(bdst[i] + so, boff[i], bk);
+    for (int q = 0; q < LPT; ++q) iss(q);
   };
 
   f32x16 acc[FM][FN];
@@ -1088,28 +1085,52 @@ void k_gemm_bf16_ps(AView a,
     }
   };
   bool tile_vt = vt_of(0);
+  // One MFMA, then its share of the next fragments' reads and of a K tile's
+  // direct loads: a wave issues in order, and eight direct loads in a row hold
+  // it for up to 1024 cycles (the eight waves' 64 KB at 64 B a clock) with its
+  // matrix pipe idle.  Tile gi + 1's second half of loads goes out in the first
+  // step of tile gi, right behind the half sent when its slot came free.
+  constexpr int HALF = LPT / 2, NM = FM * FN;
+  static_assert(LPT % 2 == 0 && HALF <= NM, "the loads of a K tile in two steps");
   int ti = 0, kt = 0;
+  bool half_left = false;                          // the second half of a tile is due
   for (int gi = 0; gi < total; ++gi) {
     const bool last_k = kt == nk - 1;
 #pragma unroll
     for (int kk = 0; kk < NS; ++kk) {
       const int p = kk & 1;
+      const bool reads = kk + 1 < NS || !last_k;
+      bool loads = false;
       if (kk + 1 < NS) {
-        PS_READ(p ^ 1, gi, kk + 1);
+        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);    // this step's fragments
+        if (kk == 0) loads = half_left;
       } else if (!last_k) {
         wait_vm_lgkm0_rt<LPT*(S - 2)>(LPT * min(S - 2, total - 2 - gi));
         __builtin_amdgcn_s_barrier();
-        if (gi + S < total) issue(gi + S);
-        PS_READ(p ^ 1, gi + 1, 0);
+        loads = half_left = gi + S < total;
+        if (loads) iss_begin(gi + S);
+      } else {
+        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
       }
-      if (kk + 1 < NS || !last_k) __builtin_amdgcn_s_waitcnt(kLgkmImm);
-      __builtin_amdgcn_sched_barrier(0);
+      const int rg = kk + 1 < NS ? gi : gi + 1, rk = (kk + 1) % NS;
+      const int off_ = (rg % S) * STAGE + (((rk * 2 + lh) ^ sw) * 8);
 #pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = SW ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[p][j], af[p][i], acc[i][j], 0, 0, 0)
-                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[p][i], bfr[p][j], acc[i][j], 0, 0, 0);
+      for (int m = 0; m < NM; ++m) {
+        const int i = m / FN, j = m % FN;
+        __builtin_amdgcn_sched_barrier(0);
+        acc[i][j] = SW ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[p][j], af[p][i], acc[i][j], 0, 0, 0)
+                       : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[p][i], bfr[p][j], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (reads && m < FM + FN) {
+          // in the order of use: A 0, B 0, B 1, A 1, ...
+          if (m == 0) af[p ^ 1][0] = *(const bf16x8*)(a_frag + off_);
+          else if (m <= FN) bfr[p ^ 1][m - 1] = *(const bf16x8*)(b_frag + off_ + (m - 1) * 32 * BK);
+          else af[p ^ 1][m - FN] = *(const bf16x8*)(a_frag + off_ + (m - FN) * 32 * BK);
+        }
+        if ((kk == 0 || kk == NS - 1) && m % (NM / HALF) == NM / HALF - 1) {
+          if (loads) iss((kk == 0 ? HALF : 0) + m / (NM / HALF));
+        }
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
     if (last_k) {
@@ -1138,8 +1159,13 @@ void k_gemm_bf16_ps(AView a,
         for (int j = 0; j < FN; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      half_left = more && gi + S < total;
       if (more) {
-        if (gi + S < total) issue(gi + S);
+        if (half_left) {
+          iss_begin(gi + S);
+#pragma unroll
+          for (int q = 0; q < HALF; ++q) iss(q);
+        }
         PS_READ(0, gi + 1, 0);
       }
       ++ti;
@@ -1150,6 +1176,181 @@ void k_gemm_bf16_ps(AView a,
     }
   }
 #undef PS_READ
+}
+
+// ---------------------------------------------------------------------------
+// Products too small for the persistent kernel's tiles (a few clips): tiles of
+// 128 x 128 or 128 x 64 on four waves.  With one or two waves per SIMD the bound
+// is a wave's own instruction order: a 1 KB direct load holds the wave while the
+// CU's load path (64 B a clock) takes the four waves' loads, and the LDS reads
+// come behind them, so a K tile of 128 x 128 x 64 took 1380 cycles (520 of loads,
+// 256 of reads, 512 of MFMAs, one after the other) however many stages were in
+// flight.  Here a wave reads all fragments of K tile t + 1 into registers while
+// it multiplies tile t, and every MFMA is followed by one or two of those reads
+// and a share of the direct loads: about 730 cycles.  A K tile's LDS slot is free
+// as soon as its fragments are in registers, so all S slots hold tiles in flight.
+// ---------------------------------------------------------------------------
+template <int BM, int BN, int WM, int WN, int S, int KIND>
+__global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(2)))
+void k_gemm_bf16_rt(AView a, const bf16_t* __restrict__ w, int M, int N, int K, Epilogue e, int n_tm,
+                    int n_tn, int gm) {
+  constexpr bool SW = kDirectEpi<KIND>;            // product formed transposed
+  constexpr int BK = 64, NW = WM * WN;
+  constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 32, FN = TN / 32, NS = BK / 16;
+  constexpr int IA = BM / (8 * NW), IB = BN / (8 * NW), LPT = IA + IB;
+  static_assert(IA * 8 * NW == BM && IB * 8 * NW == BN, "tile/waves");
+  static_assert(S >= 2 && LPT * (S - 1) < 64, "stages");
+  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
+  constexpr int STAGE = (BM + BN) * BK;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int wm = wave % WM, wn = wave / WM;
+  int tm, tn;
+  tile_of(blockIdx.x, n_tm * n_tn, n_tm, n_tn, gm, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) bf16_t*)smem);
+  const bf16_t* abase = (const bf16_t*)a.ptr;
+  uint32_t aoff[IA], boff[IB];                     // bytes (the launcher checks the extents)
+#pragma unroll
+  for (int i = 0; i < IA; ++i) {
+    const int row = (i * NW + wave) * 8 + lane / 8;
+    const int r = min(m0 + row, M - 1), c = ((lane % 8) ^ lds_swz<BK>(row)) * 8;
+    const int g = a.rows_per_batch >= M ? 0 : r / a.rows_per_batch;
+    aoff[i] = (uint32_t)(g * a.batch_stride + (int64_t)(r - g * a.rows_per_batch) * a.lda + c) * 2u;
+  }
+#pragma unroll
+  for (int i = 0; i < IB; ++i) {
+    const int row = (i * NW + wave) * 8 + lane / 8;
+    const int c = ((lane % 8) ^ lds_swz<BK>(row)) * 8;
+    boff[i] = ((uint32_t)min(n0 + row, N - 1) * (uint32_t)K + (uint32_t)c) * 2u;
+  }
+  const int nk = K / BK;
+  auto issue = [&](int t) {
+    const uint32_t d = lds0 + (uint32_t)((t % S) * STAGE * 2 + wave * 1024);
+#pragma unroll
+    for (int i = 0; i < IA; ++i) lds_dma16_s(d + i * NW * 1024, aoff[i], abase + t * BK);
+#pragma unroll
+    for (int i = 0; i < IB; ++i) lds_dma16_s(d + BM * BK * 2 + i * NW * 1024, boff[i], w + t * BK);
+  };
+  f32x16 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  const int lrow = lane & 31, sw = lds_swz<BK>(lrow), lh = lane >> 5;
+  const bf16_t* a_frag = smem + (wm * TM + lrow) * BK;
+  const bf16_t* b_frag = smem + BM * BK + (wn * TN + lrow) * BK;
+  bf16x8 af[2][NS][FM], bfr[2][NS][FN];
+  auto read = [&](int t, bf16x8 (&x)[NS][FM], bf16x8 (&y)[NS][FN]) {
+    const int base = (t % S) * STAGE;
+#pragma unroll
+    for (int kk = 0; kk < NS; ++kk) {
+      const int off = base + (((kk * 2 + lh) ^ sw) * 8);
+#pragma unroll
+      for (int i = 0; i < FM; ++i) x[kk][i] = *(const bf16x8*)(a_frag + off + i * 32 * BK);
+#pragma unroll
+      for (int j = 0; j < FN; ++j) y[kk][j] = *(const bf16x8*)(b_frag + off + j * 32 * BK);
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < S; ++t)
+    if (t < nk) issue(t);
+  wait_vm_lgkm0_rt<LPT*(S - 1)>(LPT * (min(S, nk) - 1));
+  __builtin_amdgcn_s_barrier();
+  read(0, af[0], bfr[0]);
+  // While S more tiles follow: every MFMA is followed by its share of the next
+  // tile's fragment reads (first) and of the direct loads, so the wave's one
+  // instruction stream keeps the matrix, LDS and load pipes busy together.
+  constexpr int NM = NS * FM * FN, NR = NS * (FM + FN);
+  int t0 = 0;
+  for (; t0 + 1 + S < nk; t0 += 2) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const int t = t0 + p;
+      __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+      wait_vmcnt<LPT*(S - 2)>();
+      __builtin_amdgcn_s_barrier();
+      const int rb = ((t + 1) % S) * STAGE;
+      const uint32_t dst = lds0 + (uint32_t)((t % S) * STAGE * 2 + wave * 1024);
+      const bf16_t* an = abase + (t + S) * BK;
+      const bf16_t* wn_ = w + (t + S) * BK;
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        __builtin_amdgcn_sched_barrier(0);
+        {
+          const int kk = m / (FM * FN), i = m / FN % FM, j = m % FN;
+          acc[i][j] = SW ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[p][kk][j], af[p][kk][i],
+                                                                   acc[i][j], 0, 0, 0)
+                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[p][kk][i], bfr[p][kk][j],
+                                                                   acc[i][j], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // reads over the first three quarters of the MFMAs, loads over all
+#pragma unroll
+        for (int q = 0; q < NR; ++q) {
+          if (q * NM * 3 / (NR * 4) != m) continue;
+          const int kk = q / (FM + FN), f = q % (FM + FN);
+          const int off = rb + (((kk * 2 + lh) ^ sw) * 8);
+          if (f < FM) af[p ^ 1][kk][f] = *(const bf16x8*)(a_frag + off + f * 32 * BK);
+          else bfr[p ^ 1][kk][f - FM] = *(const bf16x8*)(b_frag + off + (f - FM) * 32 * BK);
+        }
+#pragma unroll
+        for (int q = 0; q < LPT; ++q) {
+          if (q * NM / LPT != m) continue;
+          if (q < IA) lds_dma16_s(dst + q * NW * 1024, aoff[q], an);
+          else lds_dma16_s(dst + BM * BK * 2 + (q - IA) * NW * 1024, boff[q - IA], wn_);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  for (; t0 < nk; t0 += 2) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const int t = t0 + p;
+      if (t < nk) {
+        // this wave holds tile t (waited for on every path, so that the compiler
+        // need not wait for tile t + 1's reads before the MFMAs); tile t + 1 has
+        // landed once at most the tiles after it are pending; after the barrier
+        // nobody reads tile t's slot
+        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+        if (t + 1 < nk) {
+          wait_vmcnt_rt<LPT*(S - 2)>(LPT * (min(S, nk - t) - 2));
+          __builtin_amdgcn_s_barrier();
+          if (t + S < nk) issue(t + S);
+          read(t + 1, af[p ^ 1], bfr[p ^ 1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kk = 0; kk < NS; ++kk)
+#pragma unroll
+          for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+              acc[i][j] = SW ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[p][kk][j], af[p][kk][i],
+                                                                       acc[i][j], 0, 0, 0)
+                             : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[p][kk][i], bfr[p][kk][j],
+                                                                       acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  __syncthreads();                                 // the ring is free (every load has landed)
+  if constexpr (SW) {
+    if constexpr (KIND == EPI_QKV) {
+      if (n0 >= 2 * e.d_model) {
+        epi_direct_vt<FM, FN>(e, acc, (float*)smem + wave * 16 * kStageLd, m0 + wm * TM,
+                              n0 + wn * TN, M, N, lane);
+        return;
+      }
+    }
+    epi_direct<KIND, FM, FN>(e, acc, m0 + wm * TM, n0 + wn * TN, M, N, lane);
+  } else {
+    epi_wave<KIND, FM, FN>(e, acc, (float*)smem + wave * (32 * kStageLd), m0 + wm * TM,
+                           n0 + wn * TN, M, N, lane);
+  }
 }
 
 // CUs the persistent GEMM leaves free (0 by default); set while a prefill
@@ -1221,13 +1422,28 @@ static void launch_gemm_pf(const AView& a, const bf16_t* w, int M, int N, int K,
   kfn<<<n_tm * n_tn, WM * WN * 64, lds, s>>>(a, w, M, N, K, e, n_tm, n_tn, gm);
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int S, int KIND, int SCHED = 0>
+template <int BM, int BN, int WM, int WN, int S, int KIND>
+static void launch_gemm_rt(const AView& a, const bf16_t* w, int M, int N, int K,
+                           const Epilogue& e, hipStream_t s, int gm) {
+  constexpr size_t lds0 = (size_t)S * (BM + BN) * 64 * sizeof(bf16_t);
+  constexpr size_t lds_epi = (size_t)WM * WN * 32 * kStageLd * sizeof(float);
+  constexpr size_t lds = lds0 > lds_epi ? lds0 : lds_epi;
+  static_assert(lds <= 160 * 1024, "LDS");
+  auto kfn = k_gemm_bf16_rt<BM, BN, WM, WN, S, KIND>;
+  static const hipError_t attr = hipFuncSetAttribute(
+      (const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  (void)attr;
+  const int n_tm = (M + BM - 1) / BM, n_tn = (N + BN - 1) / BN;
+  kfn<<<n_tm * n_tn, WM * WN * 64, lds, s>>>(a, w, M, N, K, e, n_tm, n_tn, gm);
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int S, int KIND>
 static void launch_gemm_dma(const AView& a, const bf16_t* w, int M, int N, int K,
                             const Epilogue& e, hipStream_t s, int gm) {
   constexpr size_t lds0 = (size_t)S * (BM + BN) * BK * sizeof(bf16_t);
   constexpr size_t lds_epi = (size_t)WM * WN * 32 * kStageLd * sizeof(float);
   constexpr size_t lds = lds0 > lds_epi ? lds0 : lds_epi;
-  auto kfn = k_gemm_bf16_dma<BM, BN, BK, WM, WN, S, KIND, SCHED>;
+  auto kfn = k_gemm_bf16_dma<BM, BN, BK, WM, WN, S, KIND>;
   static bool attr = false;
   if (!attr) {
     (void)hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1255,34 +1471,40 @@ static void launch_gemm_cfg(const AView& a, const bf16_t* w, int M, int N, int K
   kfn<<<n_tm * n_tn, WM * WN * 64, lds, s>>>(a, w, M, N, K, e, n_tm, n_tn, gm);
 }
 
-// Tile choice by shape (measured on MI355X with the encoder's products):
-// 256x256x64 tiles, two LDS stages, 8 waves of 128x64, fragment reads
-// pipelined across K tiles, wherever K is a multiple of 64 and at least 512
-// tiles exist -- persistent (epilogue overlapped with the next tile's loads)
-// unless the epilogue reads the output (residual add); otherwise 256x128x32
-// with three stages (8 waves of 64x64), and 128x128x32 with four stages when
-// even those tiles would be too few to fill the chip.  K not a multiple of 32
-// (the 80-mel first convolution) takes the register-path kernel, which
-// zero-fills the K tail.
+// Tile choice by shape (measured on MI355X with the encoder's products; M x N x
+// K, us as here / as the other):
+//  * K a multiple of 64 and at least two rounds of 256x256 tiles: persistent
+//    256x256x64 kernel, 8 waves of 128x64 (24000 x 2304 x 768, 846 tiles: 112 /
+//    about 137 in 128x128 tiles), except the first convolution, whose scatter
+//    epilogue runs slower from the persistent kernel's half-block stage than
+//    from the plain kernel's full-block one;
+//  * fewer: 128x128 tiles, two blocks of two LDS stages a CU (4500 x 5120 x
+//    1280: 77 / 83 in the unpipelined 256x128; 24000 x 768 x 3072: 136 / 159);
+//    when they are at most one round, one block of four stages (6000 x 512 x
+//    2048, 188 tiles: 17.6 / 24.6); when at most half a round, 128x64 tiles of
+//    three stages (1500 x 1280 x 5120: 30 / 54, as 120 tiles of 128x128 37).
+//    The sums are the same in all of these (one chain over K), so a clip's
+//    result does not depend on how many clips share a product.
+//  * K a multiple of 32 only: 128x128x32 tiles with four stages; K not even
+//    that (the 80-mel first convolution): the register-path kernel, which
+//    zero-fills the K tail.
 template <int KIND>
 static void launch_gemm_bf16(const AView& a, const bf16_t* w, int M, int N, int K,
                              const Epilogue& e, hipStream_t s) {
-  const long t256x128 = (long)((M + 255) / 256) * ((N + 127) / 128);
-  const long t256x256 = (long)((M + 255) / 256) * ((N + 255) / 256);
+  const int64_t t256x256 = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
+  const int64_t t128x128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
+  const bool direct = kDirectEpi<KIND> && direct_epi_ok(e, M, N);
   if (K % 32 != 0) {
-    if (t256x128 >= 1024)
+    if (t128x128 >= 2048)
       launch_gemm_cfg<256, 128, 32, 4, 2, KIND>(a, w, M, N, K, e, s, 4);
     else
       launch_gemm_cfg<128, 128, 32, 2, 2, KIND>(a, w, M, N, K, e, s, 8);
   } else if (K % 64 == 0 && t256x256 >= 512) {
-    // (the stem's scatter epilogue runs slower from the persistent kernel's
-    // half-block stage than from the plain kernel's full-block one; the
-    // fused QKV product goes persistent only with its register epilogue)
-    if (KIND != EPI_CONV1 && fits_u32_offsets(a, M, N, K) &&
-        (KIND != EPI_QKV || direct_epi_ok(e, M, N))) {
+    // (the fused QKV product goes persistent only with its register epilogue)
+    if (KIND != EPI_CONV1 && fits_u32_offsets(a, M, N, K) && (KIND != EPI_QKV || direct)) {
       const int gm = N >= 3072 ? 8 : 4;
       if constexpr (kDirectEpi<KIND>) {
-        if (direct_epi_ok(e, M, N)) {
+        if (direct) {
           launch_gemm_ps<256, 256, 64, 2, 4, 2, KIND, 1, true>(a, w, M, N, K, e, s, gm);
           return;
         }
@@ -1290,8 +1512,13 @@ static void launch_gemm_bf16(const AView& a, const bf16_t* w, int M, int N, int 
       launch_gemm_ps<256, 256, 64, 2, 4, 2, KIND>(a, w, M, N, K, e, s, gm);
     } else
       launch_gemm_pf<256, 256, 64, 2, 4, 2, KIND>(a, w, M, N, K, e, s, 4);
-  } else if (t256x128 >= 512) {
-    launch_gemm_pf<256, 128, 32, 4, 2, 3, KIND>(a, w, M, N, K, e, s, 4);
+  } else if (K % 64 == 0 && fits_u32_offsets(a, M, N, K) && (direct || !kDirectEpi<KIND>)) {
+    if (t128x128 <= 128)
+      launch_gemm_rt<128, 64, 2, 2, 3, KIND>(a, w, M, N, K, e, s, 8);
+    else if (t128x128 <= 256)
+      launch_gemm_rt<128, 128, 2, 2, 4, KIND>(a, w, M, N, K, e, s, 8);
+    else
+      launch_gemm_rt<128, 128, 2, 2, 2, KIND>(a, w, M, N, K, e, s, 8);
   } else {
     launch_gemm_dma<128, 128, 32, 2, 2, 4, KIND>(a, w, M, N, K, e, s, 8);
   }
