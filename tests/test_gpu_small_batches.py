@@ -31,3 +31,15 @@ def test_clip_is_the_same_in_every_batch(n_mels, n_head, d_ffn, n):
     for g in (2, 3):
         ctx.set_encoder_streams(g)
         assert np.array_equal(ctx.debug_encode(clips), together), g
+
+
+def test_log_mel_clip_is_the_same_in_every_batch():
+    """The normalisation gives a thread 1 to 16 vectors by the batch's size: one
+    up to 8 clips of 80 filters, two from 9 and three at 17, and none of that
+    changes a value."""
+    shape = synth.ModelShape("small-batch-mel", 80, 128, 1, 0, 2, 128, 0, "bf16")
+    ctx = make_context(shape, 20260391, max_slots=0, max_prefill=17, max_decode=0)
+    clips = [synth.pcm_clip(20260391, i, 800 + 27000 * i) for i in range(17)]
+    together = ctx.debug_logmel(clips)
+    for k in (1, 8, 9):
+        assert np.array_equal(ctx.debug_logmel(clips[-k:]), together[-k:]), k
