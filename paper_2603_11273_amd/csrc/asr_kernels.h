@@ -114,8 +114,8 @@ void vocab_logits_f32(const float* x, const float* emb, int D, int V, int K, flo
                       hipStream_t s);
 void logits_argmax_keys(const float* logits, int D, int V, uint64_t* keys, int n_tiles,
                         hipStream_t s);
-void argmax_finish(const uint64_t* keys, int D, int n_tiles, int32_t* out, int32_t* nan_flag,
-                   hipStream_t s);
+// out[b] = the argmax, or -1 - argmax where its logit is a NaN.
+void argmax_finish(const uint64_t* keys, int D, int n_tiles, int32_t* out, hipStream_t s);
 int vocab_tiles(int V);
 
 // LayerNorm rows of a float32 matrix into storage type T.

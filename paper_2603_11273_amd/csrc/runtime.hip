@@ -85,9 +85,8 @@ struct Layout {
   size_t pcm_stage = 0, pcm_ptrs = 0, pcm_n = 0, mel_raw = 0, mel_gmax = 0, mel_norm = 0,
          h1 = 0, x = 0, xn = 0, qkv = 0, vt = 0, att = 0, hid = 0, p_slots = 0;
   size_t vt_bytes = 0;
-  size_t d_slots = 0, d_tokens = 0, d_pos = 0, d_h = 0, d_xn = 0, d_qkv = 0, d_att = 0,
-         d_hid = 0, d_part = 0, d_apart = 0, d_logits = 0, d_keys = 0, d_argmax = 0,
-         d_flag = 0;
+  size_t d_rows = 0, d_h = 0, d_xn = 0, d_qkv = 0, d_att = 0,
+         d_hid = 0, d_part = 0, d_apart = 0, d_logits = 0, d_keys = 0, d_argmax = 0;
   size_t wstage = 0;
   int64_t wstage_floats = 0;
   std::vector<PackOp> pack;
@@ -307,9 +306,7 @@ void plan(asr_ctx* c) {
   L.p_slots = b.take(P * 4);
   // decode scratch
   const int64_t D = std::max(1, g.max_decode);
-  L.d_slots = b.take(D * 4);
-  L.d_tokens = b.take(D * 4);
-  L.d_pos = b.take(D * 4);
+  L.d_rows = b.take(D * 12);   // a step's slots, tokens and positions, one after the other
   L.d_h = b.take(D * d * f4);
   L.d_xn = b.take(D * d * es);
   L.d_qkv = b.take(D * 3 * d * f4);
@@ -320,7 +317,6 @@ void plan(asr_ctx* c) {
   L.d_logits = b.take(D * (int64_t)std::max(1, g.vocab) * f4);
   L.d_keys = b.take(D * (int64_t)vocab_tiles(std::max(1, g.vocab)) * 8);
   L.d_argmax = b.take(D * 4);
-  L.d_flag = b.take(256);
   // staging for weight upload and debug read-back
   int64_t stage = max_param;
   stage = std::max<int64_t>(stage, P * kFrames * M);               // debug logmel
@@ -794,7 +790,7 @@ asr_status cross_kv(asr_ctx* c, const void* E, int n, int slot0) {
 }
 
 // ---------------------------------------------------------------------------
-// Decode pipeline (rows already uploaded to d_slots / d_tokens / d_pos)
+// Decode pipeline (the rows' slots, tokens and positions already in d_rows)
 // ---------------------------------------------------------------------------
 // A decode product (rows_*), timed with the traffic it cannot do without:
 // weights, operand and result once.
@@ -821,8 +817,8 @@ asr_status decode_rows(asr_ctx* c, int D, const std::vector<int32_t>& pos_host, 
   T* att = c->at<T>(L.d_att);
   T* hid = c->at<T>(L.d_hid);
   float* rec = c->at<float>(L.d_apart);
-  const int32_t* slots = c->at<int32_t>(L.d_slots);
-  const int32_t* pos = c->at<int32_t>(L.d_pos);
+  const int32_t* slots = c->at<int32_t>(L.d_rows);
+  const int32_t *tokens = slots + D, *pos = tokens + D;
   T* self_cache = c->at<T>(L.self_kv);
   T* cross_cache = c->at<T>(L.cross_kv);
   double self_keys = 0;
@@ -830,7 +826,7 @@ asr_status decode_rows(asr_ctx* c, int D, const std::vector<int32_t>& pos_host, 
   const double Dd = (double)D * d;
 
   timed(c, ASR_K_OTHER, 0.0, Dd * (c->es + 8), [&] {
-    embed<T>(c->at<T>(L.tok_emb), c->at<float>(L.pos_emb), c->at<int32_t>(L.d_tokens), pos, D, d,
+    embed<T>(c->at<T>(L.tok_emb), c->at<float>(L.pos_emb), tokens, pos, D, d,
              h, s);
   });
   // Few rows run the LayerNorms at the start of the products that follow them
@@ -902,8 +898,6 @@ asr_status decode_rows(asr_ctx* c, int D, const std::vector<int32_t>& pos_host, 
       timed(c, ASR_K_LN, 8.0 * Dd, Dd * (4 + c->es), [&] { rows_norm<T>(h, D, d, ng, nb, xn, s); });
   }
   const int nt = vocab_tiles(V);
-  int32_t* flag = c->at<int32_t>(L.d_flag);
-  fill_u32((uint32_t*)flag, 0u, 1, c->stream);
   timed(c, ASR_K_VOCAB, 2.0 * D * (double)V * d, (double)V * d * c->es + (double)D * d * c->es,
         [&] {
           if (c->bf16()) {
@@ -916,7 +910,7 @@ asr_status decode_rows(asr_ctx* c, int D, const std::vector<int32_t>& pos_host, 
             logits_argmax_keys(c->at<float>(L.d_logits), D, V, c->at<uint64_t>(L.d_keys), nt,
                                c->stream);
           }
-          argmax_finish(c->at<uint64_t>(L.d_keys), D, nt, c->at<int32_t>(L.d_argmax), flag,
+          argmax_finish(c->at<uint64_t>(L.d_keys), D, nt, c->at<int32_t>(L.d_argmax),
                         c->stream);
         });
   CHECK_LAUNCH();
@@ -1289,27 +1283,34 @@ asr_status decode_launch(asr_ctx* c, int D, const std::vector<int32_t>& pos, boo
 }
 
 // Decode rows (slot, token, position) -> argmax (and logits when asked).
-// Returns EDEVICE after the copies when a NaN logit was flagged.
+// Returns EDEVICE after the copies when an argmax is a NaN logit's.  The rows
+// go up in one copy and their results down in one: each small copy is a trip of
+// its own through the queue (one tiny fp32 row: 282 us with five copies, a flag
+// to clear and a slower argmax, 256 with two).
 asr_status run_decode(asr_ctx* c, int D, const int32_t* slots, const int32_t* tokens,
                       const std::vector<int32_t>& pos, int32_t* argmax, float* logits) {
   if (D == 0) return ASR_OK;
   hipStream_t s = c->stream;
-  HIPCHK(hipMemcpyAsync(c->at(c->L.d_slots), slots, D * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(c->at(c->L.d_tokens), tokens, D * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(c->at(c->L.d_pos), pos.data(), D * 4, hipMemcpyHostToDevice, s));
+  std::vector<int32_t> rows(slots, slots + D);   // outlives the copy: the stream is waited for
+  rows.insert(rows.end(), tokens, tokens + D);
+  rows.insert(rows.end(), pos.begin(), pos.begin() + D);
+  HIPCHK(hipMemcpyAsync(c->at(c->L.d_rows), rows.data(), rows.size() * 4, hipMemcpyHostToDevice, s));
   PhaseMark pm(c, ASR_K_DECODE);
   asr_status st = decode_launch(c, D, pos, logits != nullptr);
   if (st != ASR_OK) return st;
   pm.end();
-  int32_t flag = 0;
   HIPCHK(hipMemcpyAsync(argmax, c->at(c->L.d_argmax), D * 4, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(&flag, c->at(c->L.d_flag), 4, hipMemcpyDeviceToHost, s));
   if (logits)
     HIPCHK(hipMemcpyAsync(logits, c->at(c->L.d_logits), (size_t)D * c->cfg.vocab * 4,
                           hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
-  if (flag) return fail(ASR_EDEVICE, "NaN logit");
-  return ASR_OK;
+  bool nan = false;
+  for (int i = 0; i < D; ++i)
+    if (argmax[i] < 0) {
+      argmax[i] = -1 - argmax[i];
+      nan = true;
+    }
+  return nan ? fail(ASR_EDEVICE, "NaN logit") : ASR_OK;
 }
 
 }  // namespace

@@ -54,3 +54,23 @@ def test_rows_do_not_depend_on_the_batch(n_head, d_ffn, dtype, batches):
         st = OW.DecoderState(2, d, pre[:, 0], pre[:, 1])
         ref = OW.decoder_step(int(toks[b]), st, ckv, P, 2, n_head)
         assert rel_err(alone[b], ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("vocab,dtype", [(1, "f32"), (33, "f32"), (289, "f32"), (70001, "f32"),
+                                         (40, "bf16"), (65569, "bf16")])
+def test_argmax_over_tile_counts_and_nan_rows(vocab, dtype):
+    """One tile, a last tile of one entry, tile counts that leave a part of a
+    block over, and more tiles than a block reads in one pass; a NaN row makes the
+    step fail, and only the step that holds it."""
+    shape = synth.ModelShape("argmax", 80, 128, 0, 1, 2, 128, vocab, dtype)
+    ctx = make_context(shape, 20260392, max_slots=3, max_prefill=3, max_decode=3)
+    E = np.stack([synth.encoder_output(20260392, b, 128).numpy() for b in range(3)])
+    E[1, 7, 5] = np.nan
+    ctx.debug_set_encoder_out([0, 1, 2], [-1] * 3, [40] * 3, E)
+    for slots in ([0], [2, 0]):
+        r = ctx.step(slots=slots, tokens=[0] * len(slots), want_logits=True)
+        assert np.array_equal(r["argmax"], r["logits"].argmax(1))
+    with pytest.raises(Exception, match="NaN logit"):
+        ctx.step(slots=[0, 1, 2], tokens=[0] * 3)
+    r = ctx.step(slots=[0, 2], tokens=[0] * 2, want_logits=True)
+    assert np.array_equal(r["argmax"], r["logits"].argmax(1))
