@@ -665,8 +665,8 @@ __global__ __launch_bounds__(256) void k_cross_merge(const float* __restrict__ p
 
 // Decode self attention: one block per (row, head) over the row's position + 1
 // keys, writing the output directly.  The keys go in parts of 32 NP, so a
-// thread holds only one part's K and V rows (bf16: two parts of 224 keys, about
-// 90 VGPRs, five blocks per CU, which is what the short rows' latency needs);
+// thread holds only one part's K and V rows (bf16: three parts of 160 keys, five
+// blocks per CU, which is what the short rows' latency needs);
 // a further part, present only for rows long enough, loads its keys as soon as
 // the part before has its scores and its values once that part's weighted sum
 // is done, and joins through the usual online-softmax rescale (block-wide
