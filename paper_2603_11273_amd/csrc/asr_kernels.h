@@ -139,7 +139,7 @@ void pack_attn_operand(const float* src, int which, int rows, int d, int n_head,
                        T* qkv, T* vt, hipStream_t s);
 // Encoder self-attention over 1500 positions, qkv [B*1500][3d], out [B*1500][d].
 void flash_attn_bf16(const bf16_t* qkv, const bf16_t* vt, bf16_t* out, int B, int n_head,
-                     hipStream_t s);
+                     int clips_in_flight, hipStream_t s);
 void flash_attn_f32(const float* qkv, float* out, int B, int n_head, hipStream_t s);
 
 // Decode attention.  Self: writes k, v of each row at its slot position, then

@@ -15,6 +15,8 @@
 //    step's key and value at the slot's position.
 #include "asr_device.h"
 
+#include <algorithm>
+
 namespace asr {
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 u) {
@@ -26,7 +28,7 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 u) {
 // ---------------------------------------------------------------------------
 // Encoder flash attention (bf16)
 //
-// Block = 8 waves x 32 queries of one (clip, head); tiles of 64 keys.  K
+// Block = NW (8 or 4) waves x 32 queries of one (clip, head); tiles of 64 keys.  K
 // comes from the fused QKV buffer, V from the per-head transposed copy the
 // QKV GEMM writes (V^T[dim][position], zero past 1500).  S^T = K Q^T is
 // computed per 32-key x 32-query block, so in the MFMA output layout a lane
@@ -39,7 +41,7 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 u) {
 //    16-byte chunk of a V^T row.  Both tiles are plain [row][64] bf16 tiles
 //    with 16-byte chunks XOR-swizzled by (row / 2) % 8 (conflict-free
 //    fragment reads), double-buffered in LDS and filled by direct
-//    global-to-LDS loads (one 1 KB instruction per wave per operand): tile
+//    global-to-LDS loads (8 / NW 1 KB instructions per wave per operand): tile
 //    kt+1 is in flight while tile kt is consumed, one barrier per tile.
 //  * The probability sum uses v_dot2 on the packed bf16 probabilities (the
 //    same rounded values the P V product uses), two per instruction.
@@ -49,7 +51,7 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 u) {
 // The kernel keeps to 128 VGPRs (four waves per SIMD, two blocks per CU):
 // the exp2 work on the VALU and the MFMAs of other waves then overlap.
 // ---------------------------------------------------------------------------
-constexpr int FP_NW = 8, FP_KT = 64;
+constexpr int FP_KT = 64;
 
 __device__ __forceinline__ void fp_dma16(uint32_t lds_addr, uint32_t voff, const void* sbase) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
@@ -65,7 +67,8 @@ __device__ __forceinline__ int fp_perm(int i) {
   return (i & ~12) | ((i & 4) << 1) | ((i & 8) >> 1);
 }
 
-__global__ __launch_bounds__(FP_NW * 64) __attribute__((amdgpu_waves_per_eu(4)))
+template <int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)))
 void k_flash_bf16(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ vt,
                        bf16_t* __restrict__ out, int n_head) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -92,7 +95,7 @@ void k_flash_bf16(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ vt,
   const int d = n_head * 64, ld3 = 3 * d;
   const bf16_t* base = qkv + (int64_t)b * kCtx * ld3;
   const int half = lane >> 5, l32 = lane & 31;
-  const int q = qb * (FP_NW * 32) + wave * 32 + l32;   // this lane's query
+  const int q = qb * (NW * 32) + wave * 32 + l32;   // this lane's query
   constexpr int NT = (kCtx + FP_KT - 1) / FP_KT;
 
   // Q fragments (B operand of S^T): dims kk*16 + half*8 .. +8 of query q
@@ -107,9 +110,9 @@ void k_flash_bf16(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ vt,
     }
   }
 
-  // Direct loads: wave w fills rows 8w .. 8w+7 of both tiles; lane l lands
-  // 16 bytes at slot l % 8 of row 8w + l / 8 and fetches the chunk that the
-  // swizzle puts there.  K rows past position 1499 re-read row 1499 (their
+  // Direct loads: wave w fills rows 8w .. 8w+7 of both tiles (and, of four waves,
+  // rows 32 + 8w .. as well); lane l lands 16 bytes at slot l % 8 of row 8w + l / 8
+  // and fetches the chunk that the swizzle (the same 32 rows on) puts there.  K rows past position 1499 re-read row 1499 (their
   // scores are masked); V^T rows are padded to kVtLd >= 64 NT positions.
   const int lrow = wave * 8 + (lane >> 3);
   const int lch = (lane & 7) ^ ((lrow >> 1) & 7);
@@ -122,10 +125,13 @@ void k_flash_bf16(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ vt,
   const uint32_t v_off = (uint32_t)((lrow * kVtLd + lch * 8) * 2);
   auto issue = [&](int t) {
     const int k0 = t * FP_KT;
-    const int key = min(k0 + lrow, kCtx - 1);
     const uint32_t so = (uint32_t)((t % S) * FP_KT * 64 * 2);
-    fp_dma16(k_lds + so, (uint32_t)((key * ld3 + lch * 8) * 2), kbase);
-    fp_dma16(v_lds + so, v_off, vbase + k0);
+#pragma unroll
+    for (int r = 0; r < FP_KT; r += 8 * NW) {
+      const int key = min(k0 + r + lrow, kCtx - 1);
+      fp_dma16(k_lds + so + r * 128, (uint32_t)((key * ld3 + lch * 8) * 2), kbase);
+      fp_dma16(v_lds + so + r * 128, v_off + (uint32_t)(r * kVtLd * 2), vbase + k0);
+    }
   };
 
   // fragment read offsets (elements) within a stage
@@ -295,12 +301,29 @@ void k_flash_bf16(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ vt,
   }
 }
 
+template <int NW>
+static void launch_flash(const bf16_t* qkv, const bf16_t* vt, bf16_t* out, int B, int n_head,
+                         hipStream_t s) {
+  dim3 grid((kCtx + NW * 32 - 1) / (NW * 32), n_head, B);
+  k_flash_bf16<NW><<<grid, NW * 64, 0, s>>>(qkv, vt, out, n_head);
+}
+
+// Waves of a block: four while the eight-wave blocks of all clips in flight (the
+// groups of a batch run beside each other) would leave half of the 256 CUs idle,
+// as 4-wave blocks then still have a CU each: encode of one large-v3 clip, 120
+// blocks of eight waves, 4668 us, 240 of four 4459 (one small clip 1252, 1170; two
+// base clips beside each other 735, 722).  With more they share CUs and
+// fetch K and V twice as often: seven base clips (336 blocks) 1500 us with
+// eight waves, 1550 with four; 32 small ones 17124, 17321.  A wave's work is the
+// same in both, and so are the results.
 void flash_attn_bf16(const bf16_t* qkv, const bf16_t* vt, bf16_t* out, int B, int n_head,
-                     hipStream_t s) {
+                     int clips_in_flight, hipStream_t s) {
   if (B <= 0) return;
   static_assert(kVtLd >= FP_KT * ((kCtx + FP_KT - 1) / FP_KT), "V^T rows cover every tile");
-  dim3 grid((kCtx + FP_NW * 32 - 1) / (FP_NW * 32), n_head, B);
-  k_flash_bf16<<<grid, FP_NW * 64, 0, s>>>(qkv, vt, out, n_head);
+  if ((int64_t)((kCtx + 255) / 256) * n_head * std::max(B, clips_in_flight) <= 128)
+    launch_flash<4>(qkv, vt, out, B, n_head, s);
+  else
+    launch_flash<8>(qkv, vt, out, B, n_head, s);
 }
 
 // Lays given q / k / v ([B*1500][d] float32) out as the encoder attention

@@ -710,7 +710,7 @@ asr_status encode_clips(asr_ctx* c, int n, bool xkv = false) {
               if (c->bf16())
                 flash_attn_bf16((const bf16_t*)qkv,
                                 c->at<bf16_t>(L.vt) + (int64_t)clip0[grp] * H * kHeadDim * kVtLd,
-                                (bf16_t*)att, ng, H, c->stream);
+                                (bf16_t*)att, ng, H, n, c->stream);
               else
                 flash_attn_f32((const float*)qkv, (float*)att, ng, H, c->stream);
             });
@@ -1770,7 +1770,7 @@ asr_status asr_debug_attention(asr_ctx* c, const float* q, const float* k, const
   }
   if (c->bf16()) {
     flash_attn_bf16(c->at<bf16_t>(L.qkv), c->at<bf16_t>(L.vt), c->at<bf16_t>(L.att), n, H,
-                    c->stream);
+                    n, c->stream);
     convert_to_f32<bf16_t>(c->at<bf16_t>(L.att), tmp, cnt, c->stream);
   } else {
     flash_attn_f32(c->at<float>(L.qkv), c->at<float>(L.att), n, H, c->stream);

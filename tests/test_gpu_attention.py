@@ -61,3 +61,16 @@ def test_attention_block_count_not_a_multiple_of_eight(n):
         ref = OW.attention(qn[b], k[b].astype(np.float64), v[b].astype(np.float64), shape.n_head)
         e = rel_err(got[b], ref)
         assert e <= ATT_TOL["bf16"], f"clip {b}: rel err {e:.3e}"
+
+
+@pytest.mark.parametrize("case", synth.ATTENTION_CASES)
+def test_attention_clip_is_the_same_in_four_and_eight_wave_blocks(case):
+    """Three clips of 8 heads are past the 128 blocks up to which a block has four
+    waves, one or two clips are not: the same bits for a clip either way."""
+    shape = synth.reduced_shape(synth.SHAPES["base"], 1, 0)
+    assert shape.n_head == 8 and shape.dtype == "bf16"
+    ctx = make_context(shape, 20260352, max_slots=0, max_prefill=3, max_decode=0)
+    q, k, v = synth.attention_operands(20260352, 3, shape.d_model, case)
+    together = ctx.debug_attention(q, k, v)
+    for n in (1, 2):
+        assert np.array_equal(ctx.debug_attention(q[:n], k[:n], v[:n]), together[:n]), n
