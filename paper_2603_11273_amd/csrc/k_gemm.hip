@@ -34,15 +34,7 @@ __device__ __forceinline__ void epi_apply(const Epilogue& e, int r, int n, float
     ((float*)e.out)[(int64_t)r * e.ldc + n] = gelu_erf(v) + e.pos[(int64_t)t * e.ldc + n];
   } else if constexpr (KIND == EPI_XKV) {
     int g = r / kCtx, t = r - g * kCtx;
-    int two_d = 2 * e.d_model;
-    int l = n / two_d;
-    int rem = n - l * two_d;
-    int kv = rem >= e.d_model;
-    int hd = rem - kv * e.d_model;
-    int h = hd >> 6, c = hd & 63;
-    int64_t addr = (int64_t)e.slots[g] * e.slot_stride +
-                   ((((int64_t)l * 2 + kv) * e.n_head + h) * kCtx + t) * kHeadDim + c;
-    St<T>::st((T*)e.out, addr, v);
+    St<T>::st((T*)e.out, (int64_t)e.slots[g] * e.slot_stride + xkv_col(n) + t * kHeadDim, v);
   } else if constexpr (KIND == EPI_QKV) {
     const int two_d = 2 * e.d_model;
     if (n < two_d) {
@@ -102,13 +94,7 @@ __device__ __forceinline__ void epi_apply4(const Epilogue& e, int r, int n, floa
             add4(gelu4(v), *(const float4*)(e.pos + (int64_t)t * e.ldc + n)));
   } else if constexpr (KIND == EPI_XKV) {
     const int g = r / kCtx, t = r - g * kCtx;
-    const int two_d = 2 * e.d_model;
-    const int l = n / two_d, rem = n - l * two_d;
-    const int kv = rem >= e.d_model, hd = rem - kv * e.d_model;
-    const int64_t addr = (int64_t)e.slots[g] * e.slot_stride +
-                         ((((int64_t)l * 2 + kv) * e.n_head + (hd >> 6)) * kCtx + t) * kHeadDim +
-                         (hd & 63);
-    st4_bf16((bf16_t*)e.out + addr, v);
+    st4_bf16((bf16_t*)e.out + (int64_t)e.slots[g] * e.slot_stride + xkv_col(n) + t * kHeadDim, v);
   }
 }
 
@@ -799,8 +785,8 @@ __device__ __forceinline__ void epi_wave_half(const Epilogue& e, f32x16 (&acc)[F
 // offset beyond it, which the hardware drops, so no lane diverges.  The
 // cross-attention cache (XKV, far above the 2^31-byte reach of a buffer
 // offset) is addressed per lane: the row part (slot, position) once per
-// tile, the column part (layer, K/V, head, dim) per 16-byte run, which an
-// eight-column run never splits since heads are 64 wide.  No LDS round trip:
+// tile, the column part (layer, K/V, head, dim) once per wave, whose columns
+// stay within one head.  No LDS round trip:
 // the store stream issues as fast as the accumulators convert.
 // Cache policy of the register epilogue's stores: the default.  Unlike the
 // staged epilogue's full-row stores, each of these instructions writes
@@ -873,21 +859,18 @@ __device__ __forceinline__ void epi_direct(const Epilogue& e, f32x16 (&acc)[FM][
   const int l32 = lane & 31, lh = lane >> 5;
   __amdgpu_buffer_rsrc_t rs;
   int64_t xrow[FM];    // XKV: slot and position part of each of the lane's rows
-  int64_t xcol = 0;    // XKV: (layer, K/V, head) part of the wave's columns
+  int64_t xcol = 0;    // XKV: (layer, K/V, head, dim) part of the wave's first column
   if constexpr (KIND == EPI_XKV) {
-    static_assert(FN * 32 <= kHeadDim, "a wave's columns stay within one head");
+    static_assert(kHeadDim % (FN * 32) == 0, "a wave's columns stay within one head");
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
       const int r = min(m0w + i * 32 + l32, M - 1), g = r / kCtx;
       xrow[i] = (int64_t)e.slots[g] * e.slot_stride + (int64_t)(r - g * kCtx) * kHeadDim;
     }
-    // the wave's FN * 32 <= 64 columns start at a multiple of 64, and
-    // d_model is one too, so they lie in one layer, one of K / V and one
-    // head: that part of the address is wave-uniform
-    const int two_d = 2 * e.d_model;
-    const int l = n0w / two_d, rem = n0w - l * two_d;
-    const int kv = rem >= e.d_model, hd0 = rem - kv * e.d_model;
-    xcol = ((((int64_t)l * 2 + kv) * e.n_head + (hd0 >> 6)) * kCtx) * kHeadDim;
+    // the wave's 32 or 64 columns start at a multiple of their number, so they
+    // lie in one layer, one of K / V and one head, and follow each other from
+    // the first one's address
+    xcol = xkv_col(n0w);
   } else {
     rs = __builtin_amdgcn_make_buffer_rsrc(e.out, (short)0, (int)((int64_t)M * e.ldc * 2),
                                            0x00020000);
