@@ -1282,18 +1282,11 @@ asr_status decode_launch(asr_ctx* c, int D, const std::vector<int32_t>& pos, boo
   return ASR_OK;
 }
 
-// Decode rows (slot, token, position) -> argmax (and logits when asked).
-// Returns EDEVICE after the copies when an argmax is a NaN logit's.  The rows
-// go up in one copy and their results down in one: each small copy is a trip of
-// its own through the queue (one tiny fp32 row: 282 us with five copies, a flag
-// to clear and a slower argmax, 256 with two).
-asr_status run_decode(asr_ctx* c, int D, const int32_t* slots, const int32_t* tokens,
-                      const std::vector<int32_t>& pos, int32_t* argmax, float* logits) {
-  if (D == 0) return ASR_OK;
+// Enqueues a step of D rows ([3][D]: slots, tokens, positions) and the copies of
+// its results.
+asr_status enqueue_decode(asr_ctx* c, int D, const std::vector<int32_t>& rows,
+                          const std::vector<int32_t>& pos, int32_t* argmax, float* logits) {
   hipStream_t s = c->stream;
-  std::vector<int32_t> rows(slots, slots + D);   // outlives the copy: the stream is waited for
-  rows.insert(rows.end(), tokens, tokens + D);
-  rows.insert(rows.end(), pos.begin(), pos.begin() + D);
   HIPCHK(hipMemcpyAsync(c->at(c->L.d_rows), rows.data(), rows.size() * 4, hipMemcpyHostToDevice, s));
   PhaseMark pm(c, ASR_K_DECODE);
   asr_status st = decode_launch(c, D, pos, logits != nullptr);
@@ -1303,7 +1296,26 @@ asr_status run_decode(asr_ctx* c, int D, const int32_t* slots, const int32_t* to
   if (logits)
     HIPCHK(hipMemcpyAsync(logits, c->at(c->L.d_logits), (size_t)D * c->cfg.vocab * 4,
                           hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
+  return ASR_OK;
+}
+
+// Decode rows (slot, token, position) -> argmax (and logits when asked).
+// Returns EDEVICE after the copies when an argmax is a NaN logit's.  The rows
+// go up in one copy and their results down in one: each small copy is a trip of
+// its own through the queue (one tiny fp32 row: 282 us with five copies, a flag
+// to clear and a slower argmax, 256 with two).
+asr_status run_decode(asr_ctx* c, int D, const int32_t* slots, const int32_t* tokens,
+                      const std::vector<int32_t>& pos, int32_t* argmax, float* logits) {
+  if (D == 0) return ASR_OK;
+  std::vector<int32_t> rows(slots, slots + D);
+  rows.insert(rows.end(), tokens, tokens + D);
+  rows.insert(rows.end(), pos.begin(), pos.begin() + D);
+  const asr_status st = enqueue_decode(c, D, rows, pos, argmax, logits);
+  // also where the step failed half way: the copies enqueued by then use `rows`
+  // and the caller's arrays
+  const hipError_t synced = hipStreamSynchronize(c->stream);
+  if (st != ASR_OK) return st;
+  HIPCHK(synced);
   bool nan = false;
   for (int i = 0; i < D; ++i)
     if (argmax[i] < 0) {
