@@ -1468,17 +1468,20 @@ static void launch_gemm_cfg(const AView& a, const bf16_t* w, int M, int N, int K
 //    three stages (1500 x 1280 x 5120: 30 / 54, as 120 tiles of 128x128 37).
 //    The sums are the same in all of these (one chain over K), so a clip's
 //    result does not depend on how many clips share a product.
-//  * K a multiple of 32 only: 128x128x32 tiles with four stages; K not even
-//    that (the 80-mel first convolution): the register-path kernel, which
-//    zero-fills the K tail.
+//  * K a multiple of 32 only (the first convolution of 32 or 96 filters): two
+//    rounds of 256x128x32 tiles or more with three stages (96000 x 1280 x 288:
+//    153 / 186 in 128x128x32, 24000 rows 47 / 55, 15000 rows, 590 tiles, 34.5 /
+//    35.7), 128x128x32 with four stages below; K not even that (the 80-mel first
+//    convolution): the register-path kernel, which zero-fills the K tail.
 template <int KIND>
 static void launch_gemm_bf16(const AView& a, const bf16_t* w, int M, int N, int K,
                              const Epilogue& e, hipStream_t s) {
   const int64_t t256x256 = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
+  const int64_t t256x128 = (int64_t)((M + 255) / 256) * ((N + 127) / 128);
   const int64_t t128x128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
   const bool direct = kDirectEpi<KIND> && direct_epi_ok(e, M, N);
   if (K % 32 != 0) {
-    if (t128x128 >= 2048)
+    if (t256x128 >= 1024)
       launch_gemm_cfg<256, 128, 32, 4, 2, KIND>(a, w, M, N, K, e, s, 4);
     else
       launch_gemm_cfg<128, 128, 32, 2, 2, KIND>(a, w, M, N, K, e, s, 8);
@@ -1502,6 +1505,8 @@ static void launch_gemm_bf16(const AView& a, const bf16_t* w, int M, int N, int 
       launch_gemm_rt<128, 128, 2, 2, 4, KIND>(a, w, M, N, K, e, s, 8);
     else
       launch_gemm_rt<128, 128, 2, 2, 2, KIND>(a, w, M, N, K, e, s, 8);
+  } else if (KIND == EPI_CONV1 && t256x128 >= 512) {
+    launch_gemm_pf<256, 128, 32, 4, 2, 3, KIND>(a, w, M, N, K, e, s, 4);
   } else {
     launch_gemm_dma<128, 128, 32, 2, 2, 4, KIND>(a, w, M, N, K, e, s, 8);
   }

@@ -15,6 +15,7 @@ pytestmark = [pytest.mark.gpu, needs_gpu]
 
 @pytest.mark.parametrize("n_mels,n_head,d_ffn,n", [
     (128, 2, 128, 3), (80, 4, 1152, 6), (128, 10, 2560, 9), (96, 6, 384, 4), (64, 20, 5120, 5),
+    (96, 20, 1280, 5),
 ])
 def test_clip_is_the_same_in_every_batch(n_mels, n_head, d_ffn, n):
     shape = synth.ModelShape("small-batch", n_mels, 64 * n_head, 2, 0, n_head, d_ffn, 0, "bf16")
