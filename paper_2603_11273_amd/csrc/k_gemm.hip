@@ -1074,7 +1074,8 @@ void k_gemm_bf16_ps(AView a,
   // matrix pipe idle.  Tile gi + 1's second half of loads goes out in the first
   // step of tile gi, right behind the half sent when its slot came free.
   constexpr int HALF = LPT / 2, NM = FM * FN;
-  static_assert(LPT % 2 == 0 && HALF <= NM, "the loads of a K tile in two steps");
+  static_assert(LPT % 2 == 0 && NM % HALF == 0, "the loads of a K tile in two steps");
+  static_assert(FM + FN <= NM, "a fragment read behind an MFMA each");
   int ti = 0, kt = 0;
   bool half_left = false;                          // the second half of a tile is due
   for (int gi = 0; gi < total; ++gi) {
