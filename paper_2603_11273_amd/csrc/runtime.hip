@@ -86,7 +86,7 @@ struct Layout {
          h1 = 0, x = 0, xn = 0, qkv = 0, vt = 0, att = 0, hid = 0, p_slots = 0;
   size_t vt_bytes = 0;
   size_t d_rows = 0, d_h = 0, d_xn = 0, d_qkv = 0, d_att = 0,
-         d_hid = 0, d_part = 0, d_apart = 0, d_logits = 0, d_keys = 0, d_argmax = 0;
+         d_hid = 0, d_part = 0, d_logits = 0, d_keys = 0, d_argmax = 0;
   size_t wstage = 0;
   int64_t wstage_floats = 0;
   std::vector<PackOp> pack;
@@ -312,8 +312,10 @@ void plan(asr_ctx* c) {
   L.d_qkv = b.take(D * 3 * d * f4);
   L.d_att = b.take(D * d * es);
   L.d_hid = b.take(D * F * es);
-  L.d_part = b.take(rows_part_floats((int)D, (int)d) * f4);
-  L.d_apart = b.take((int64_t)decode_attn_part_floats((int)D, g.n_head) * f4);
+  // the records of a layer's cross attention, then (they are merged by then) the
+  // partial sums of its FC2
+  L.d_part = b.take(std::max<size_t>(rows_part_floats((int)D, (int)d),
+                                     decode_attn_part_floats((int)D, g.n_head)) * f4);
   L.d_logits = b.take(D * (int64_t)std::max(1, g.vocab) * f4);
   L.d_keys = b.take(D * (int64_t)vocab_tiles(std::max(1, g.vocab)) * 8);
   L.d_argmax = b.take(D * 4);
@@ -816,7 +818,7 @@ asr_status decode_rows(asr_ctx* c, int D, const std::vector<int32_t>& pos_host, 
   float* qkv = c->at<float>(L.d_qkv);               // also the cross queries
   T* att = c->at<T>(L.d_att);
   T* hid = c->at<T>(L.d_hid);
-  float* rec = c->at<float>(L.d_apart);
+  float* part = c->at<float>(L.d_part);
   const int32_t* slots = c->at<int32_t>(L.d_rows);
   const int32_t *tokens = slots + D, *pos = tokens + D;
   T* self_cache = c->at<T>(L.self_kv);
@@ -869,14 +871,14 @@ asr_status decode_rows(asr_ctx* c, int D, const std::vector<int32_t>& pos_host, 
     norm_product(w.lnx_g, w.lnx_b, w.xq_w, w.xq_b, d, false, qkv);
     const int64_t cross_off = (int64_t)l * 2 * H * kCtx * kHeadDim;
     timed(c, ASR_K_DATTN, 4.0 * Dd * kCtx, Dd * kCtx * 2 * c->es, [&] {
-      decode_cross_attn<T>(qkv, cross_cache, L.cross_stride, cross_off, slots, D, H, rec, s);
+      decode_cross_attn<T>(qkv, cross_cache, L.cross_stride, cross_off, slots, D, H, part, s);
     });
     if (D <= kMergeRows) {
       drows<T>(c, D, d, d, Dd * (c->es + 8), [&] {
-        rows_merge_resid<T>(rec, c->at<T>(w.xo_w), c->at<float>(w.xo_b), D, d, h, s);
+        rows_merge_resid<T>(part, c->at<T>(w.xo_w), c->at<float>(w.xo_b), D, d, h, s);
       });
     } else {
-      timed(c, ASR_K_DATTN, 0.0, 0.0, [&] { decode_cross_merge<T>(rec, D, H, att, s); });
+      timed(c, ASR_K_DATTN, 0.0, 0.0, [&] { decode_cross_merge<T>(part, D, H, att, s); });
       resid_product(att, w.xo_w, w.xo_b);
     }
     norm_product(w.ln2_g, w.ln2_b, w.fc1_w, w.fc1_b, F, true, hid);
@@ -887,7 +889,7 @@ asr_status decode_rows(asr_ctx* c, int D, const std::vector<int32_t>& pos_host, 
       if constexpr (sizeof(T) == 2) {
         if (wide) {
           rows_resid_norm(hid, c->at<T>(w.fc2_w), c->at<float>(w.fc2_b), D, d, F, h, ng, nb, xn,
-                          c->at<float>(L.d_part), s);
+                          part, s);
           normed = true;
           return;
         }

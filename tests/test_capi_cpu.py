@@ -63,6 +63,21 @@ def test_create_rejects_bad_shapes(field, value):
     assert e.value.status == asr.ASR_EINVAL
 
 
+@pytest.mark.parametrize("name,caps,block", [
+    ("tiny", (2, 1, 1), 310354176), ("tiny", (192, 64, 128), 6942224896),
+    ("base", (32, 4, 32), 1129982976), ("small", (64, 16, 64), 5838896128),
+    ("large-v3", (2, 1, 1), 4283858944), ("large-v3", (192, 64, 128), 68670906368),
+])
+def test_workspace_fits_blocks_of_earlier_sizes(name, caps, block):
+    """A block that held a context of these capacities (slots, prefill, decode)
+    still does: bytes needed before the decode step had scratch for chunk records
+    and partial sums apart."""
+    from paper_2603_11273_amd import synth
+    s, p, d = caps
+    cfg = asr.model_cfg(synth.SHAPES[name], max_slots=s, max_prefill=p, max_decode=d)
+    assert asr.Context(cfg, device=-1).workspace_size() <= block
+
+
 def test_submit_validation():
     ctx = asr.Context(_tiny_cfg(max_queue=2), device=-1)
     pcm = np.zeros(1600, np.float32)
