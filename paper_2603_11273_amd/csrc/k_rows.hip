@@ -19,7 +19,7 @@
 
 namespace asr {
 
-constexpr int RL_LW = 8;             // waves that prepare x
+constexpr int RL_LW = 8;             // waves that prepare x, and the most rows that are prepared
 constexpr int RL_RB = 32;            // decode rows of a block at most
 constexpr size_t RL_LDS = 160 * 1024;
 
@@ -70,13 +70,11 @@ __global__ __launch_bounds__((S + (X == RX_MEM ? 0 : RL_LW)) * 64) void k_rows(R
   if (X != RX_MEM && wave >= S) {
     const int lw = wave - S;
     if constexpr (X == RX_LN) {
-      RowLN<NV> ln;
-      const float* hr = (const float*)a.x + (int64_t)row0 * a.K;
-      ln.row(hr + (int64_t)min(lw, rows - 1) * a.K, a.K, lane);
-      ln.params(a.g, a.beta, a.K, lane);
-      for (int r = lw; r < rows; r += RL_LW) {
-        if (r != lw) ln.row(hr + (int64_t)r * a.K, a.K, lane);
-        ln.template write<T>((T*)(xs + r * xld), a.K, lane);
+      if (lw < rows) {
+        RowLN<NV> ln;
+        ln.row((const float*)a.x + (int64_t)(row0 + lw) * a.K, a.K, lane);
+        ln.params(a.g, a.beta, a.K, lane);
+        ln.template write<T>((T*)(xs + lw * xld), a.K, lane);
       }
     } else {
       const int n_head = a.K / kHeadDim;
@@ -189,17 +187,21 @@ __global__ __launch_bounds__((S + (X == RX_MEM ? 0 : RL_LW)) * 64) void k_rows(R
   }
 }
 
+// Decode rows of a block at most.
+template <int X>
+constexpr int kBlockRows = X == RX_MEM ? RL_RB : RL_LW;
+
 template <typename T, int X, int EPI, int S, int WR8, int NV>
-static bool launch_rows(RowsArgs a, hipStream_t s) {
+static void launch_rows(RowsArgs a, hipStream_t s) {
   const int kb = a.K * (int)sizeof(T);
-  // decode rows of a block: as many as the prepared rows leave LDS for
-  a.rb = std::min(a.D, RL_RB);
-  const size_t least = (size_t)S * WR8 * 1024;         // one ring stage
-  if (X != RX_MEM)
-    while (a.rb > 1 && a.rb * (size_t)(kb + 16) + least > RL_LDS) a.rb = (a.rb + 1) / 2;
+  a.rb = std::min(a.D, kBlockRows<X>);
+  // LDS: the prepared rows, and as many ring stages as a wave has chunks or fit
+  constexpr int kWidest = 2048;                        // K of prepared rows at most
+  static_assert((X == RX_MEM ? 0 : (size_t)RL_LW * (kWidest * sizeof(T) + 16)) +
+                        (size_t)S * (WR8 + (X == RX_MEM ? RL_RB / 8 : 0)) * 1024 <= RL_LDS,
+                "one ring stage fits");
   const size_t xbytes = X == RX_MEM ? 0 : (size_t)a.rb * (kb + 16);
   const size_t stage = (size_t)S * (WR8 + (X == RX_MEM ? (a.rb + 7) / 8 : 0)) * 1024;
-  if (xbytes + stage > RL_LDS) return false;
   a.ring = (int)std::min<size_t>((kb / 128 + S - 1) / S, (RL_LDS - xbytes) / stage);
   auto kfn = k_rows<T, X, EPI, S, WR8, NV>;
   static const hipError_t attr = hipFuncSetAttribute(
@@ -207,7 +209,6 @@ static bool launch_rows(RowsArgs a, hipStream_t s) {
   (void)attr;
   constexpr int NT = (S + (X == RX_MEM ? 0 : RL_LW)) * 64;
   kfn<<<dim3(a.N / (8 * WR8), (a.D + a.rb - 1) / a.rb), NT, xbytes + a.ring * stage, s>>>(a);
-  return true;
 }
 
 // Weight rows of a block: the fewest that keep the grid within one block a CU
@@ -215,11 +216,10 @@ static bool launch_rows(RowsArgs a, hipStream_t s) {
 // 240 of 16 6.2 us, 120 of 32 7.2, 480 of 8 7.7).
 template <typename T, int X, int EPI, int S, int NV = 1>
 static void launch_rows_any(const RowsArgs& a, hipStream_t s) {
-  const int ny = (a.D + RL_RB - 1) / RL_RB;
-  const bool fits8 = (int64_t)(a.N / 8) * ny <= 256, fits16 = (int64_t)(a.N / 16) * ny <= 256;
-  if (!fits8 && !fits16 && launch_rows<T, X, EPI, S, 4, NV>(a, s)) return;
-  if (!fits8 && launch_rows<T, X, EPI, S, 2, NV>(a, s)) return;
-  (void)launch_rows<T, X, EPI, S, 1, NV>(a, s);        // fits LDS: 8 KB a stage beside one row
+  const int ny = (a.D + kBlockRows<X> - 1) / kBlockRows<X>;
+  if ((int64_t)(a.N / 8) * ny <= 256) launch_rows<T, X, EPI, S, 1, NV>(a, s);
+  else if ((int64_t)(a.N / 16) * ny <= 256) launch_rows<T, X, EPI, S, 2, NV>(a, s);
+  else launch_rows<T, X, EPI, S, 4, NV>(a, s);
 }
 
 // ---------------------------------------------------------------------------

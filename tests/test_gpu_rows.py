@@ -1,9 +1,11 @@
 """A decode row's logits do not depend on the rows beside it: the same rows,
 alone, in small batches and in batches past the 32 rows of a block (which take
-other block shapes, and the merge of the cross attention's key chunks in a
-kernel of its own), give the same bits, and the single rows match the oracle.
-The widths reach the products' limits: a K of fewer chunks than a block has
-waves, LDS too small for 32 prepared rows, an MLP that is not a power of two."""
+other block shapes), give the same bits, and the single rows match the oracle.
+Batches on both sides of the lines at which the LayerNorms (8 rows) and the merge
+of the cross attention's key chunks (4) become kernels of their own, and rows
+from every block of 32.  The widths reach the products' limits: a K of fewer
+chunks than a block has waves, the widest rows, an MLP that is not a power of
+two."""
 import numpy as np
 import pytest
 
@@ -16,9 +18,9 @@ pytestmark = [pytest.mark.gpu, needs_gpu]
 
 
 @pytest.mark.parametrize("n_head,d_ffn,dtype,batches", [
-    (1, 64, "f32", [2, 5, 33]), (6, 1536, "f32", [3, 34, 128]), (20, 1344, "f32", [4, 17, 40]),
-    (2, 128, "bf16", [2, 31, 65]), (12, 3072, "bf16", [4, 5, 33, 128]),
-    (20, 5120, "bf16", [5, 40]), (32, 1920, "bf16", [5, 36]),
+    (1, 64, "f32", [2, 5, 33]), (6, 1536, "f32", [3, 8, 9, 34, 128]), (20, 1344, "f32", [4, 17, 40]),
+    (2, 128, "bf16", [2, 31, 65]), (12, 3072, "bf16", [4, 5, 8, 9, 32, 33, 128]),
+    (20, 5120, "bf16", [5, 40]), (32, 1920, "bf16", [5, 8, 36]), (32, 128, "f32", [8, 9]),
 ])
 def test_rows_do_not_depend_on_the_batch(n_head, d_ffn, dtype, batches):
     d = 64 * n_head
@@ -40,7 +42,7 @@ def test_rows_do_not_depend_on_the_batch(n_head, d_ffn, dtype, batches):
             ctx.debug_set_self_kv(b, kv[b % 3], lengths[b])
         return ctx.step(slots=rows, tokens=[int(toks[b]) for b in rows], want_logits=True)["logits"]
 
-    some = [0, 1, 2, 4]
+    some = [0, 1, 2, 4, 7, 8, 31, 32, 33, 63, 64, 95, 96, B - 1]
     alone = {b: step([b])[0] for b in some if b < B}
     for n in batches:
         got = step(list(range(n)))
