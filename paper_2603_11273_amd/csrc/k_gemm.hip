@@ -1653,13 +1653,18 @@ static void launch_gemm_f32_cfg(const AView& a, const float* w, int M, int N, in
   k_gemm_f32<KIND, WM, WN><<<n_tm * n_tn, WM * WN * 256, lds, s>>>(a, w, M, N, K, e, n_tm, n_tn, 4);
 }
 
-// 64x64 tiles (16 waves) halve the operand traffic and take over where they
-// give every CU two blocks: 12000 x 1536 x 384 in halves 164 us against 190,
-// 1500 x 1536 x 384 (576 tiles) 31.6 against 30.2.
+// 64x64 tiles (16 waves) halve the operand traffic.  They take over from 577 of
+// them on, past two rounds of one block a CU: 12000 x 1536 x 384 in halves 164 us
+// against 190 in 32x32, 4500 rows of the same (1704 tiles; the encode of three
+// tiny clips) 1672 against 1720; at 576 (1500 x 1536 x 384) the 32x32 ones still
+// take 30.2 against 31.6.  Not where one 32-row tile holds all rows (the
+// vocabulary product of a few decode rows): half of the tile would be padding, a
+// tiny step of one row 235 us in 32x32 tiles, 245 in 64x64, of 32 rows 389 and
+// 397; of 33 rows 415 and 410.
 template <int KIND>
 static void launch_gemm_f32(const AView& a, const float* w, int M, int N, int K,
                             const Epilogue& e, hipStream_t s) {
-  if ((int64_t)((M + 63) / 64) * ((N + 63) / 64) > 576)
+  if (M > 32 && (int64_t)((M + 63) / 64) * ((N + 63) / 64) > 576)
     launch_gemm_f32_cfg<KIND, 2, 2>(a, w, M, N, K, e, s);
   else
     launch_gemm_f32_cfg<KIND, 1, 1>(a, w, M, N, K, e, s);

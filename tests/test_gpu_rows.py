@@ -2,8 +2,9 @@
 alone, in small batches and in batches past the 32 rows of a block (which take
 other block shapes), give the same bits, and the single rows match the oracle.
 Batches on both sides of the lines at which the LayerNorms (8 rows) and the merge
-of the cross attention's key chunks (4) become kernels of their own, and rows
-from every block of 32.  The widths reach the products' limits: a K of fewer
+of the cross attention's key chunks (2) become kernels of their own and the
+float32 vocabulary product changes its tiles (32), and rows from every block of
+32.  The widths reach the products' limits: a K of fewer
 chunks than a block has waves, the widest rows, an MLP that is not a power of
 two."""
 import numpy as np
@@ -17,14 +18,16 @@ from gpu_util import TOL, cpu_params, make_context, needs_gpu, rel_err
 pytestmark = [pytest.mark.gpu, needs_gpu]
 
 
-@pytest.mark.parametrize("n_head,d_ffn,dtype,batches", [
-    (1, 64, "f32", [2, 5, 33]), (6, 1536, "f32", [3, 8, 9, 34, 128]), (20, 1344, "f32", [4, 17, 40]),
-    (2, 128, "bf16", [2, 31, 65]), (12, 3072, "bf16", [4, 5, 8, 9, 32, 33, 128]),
-    (20, 5120, "bf16", [5, 40]), (32, 1920, "bf16", [5, 8, 36]), (32, 128, "f32", [8, 9]),
+@pytest.mark.parametrize("n_head,d_ffn,vocab,dtype,batches", [
+    (1, 64, 40000, "f32", [2, 5, 32, 33]), (6, 1536, 500, "f32", [2, 3, 8, 9, 34, 128]),
+    (20, 1344, 500, "f32", [4, 17, 40]),
+    (2, 128, 500, "bf16", [2, 31, 65]), (12, 3072, 500, "bf16", [2, 3, 4, 5, 8, 9, 32, 33, 128]),
+    (20, 5120, 500, "bf16", [3, 5, 40]), (32, 1920, 500, "bf16", [2, 5, 8, 36]),
+    (32, 128, 500, "f32", [8, 9]),
 ])
-def test_rows_do_not_depend_on_the_batch(n_head, d_ffn, dtype, batches):
+def test_rows_do_not_depend_on_the_batch(n_head, d_ffn, vocab, dtype, batches):
     d = 64 * n_head
-    shape = synth.ModelShape("rows", 80, d, 0, 2, n_head, d_ffn, 500, dtype)
+    shape = synth.ModelShape("rows", 80, d, 0, 2, n_head, d_ffn, vocab, dtype)
     seed = 20260370 + n_head
     B = max(batches)
     ctx = make_context(shape, seed, max_slots=B, max_prefill=8, max_decode=B)
