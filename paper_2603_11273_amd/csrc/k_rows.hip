@@ -213,13 +213,15 @@ static void launch_rows(RowsArgs a, hipStream_t s) {
 
 // Weight rows of a block: the fewest that keep the grid within one block a CU
 // (FC1 of one row at d = 1280: 320 blocks of 16 rows 8.8 us, 160 of 32 7.6; QKV:
-// 240 of 16 6.2 us, 120 of 32 7.2, 480 of 8 7.7).
+// 240 of 16 6.2 us, 120 of 32 7.2, 480 of 8 7.7).  The kernels lie in the code
+// object in the order of these branches: the other way round, the same code, steps
+// of 9 to 32 large-v3 rows took 0.5 % longer (3210 -> 3225 us).
 template <typename T, int X, int EPI, int S, int NV = 1>
 static void launch_rows_any(const RowsArgs& a, hipStream_t s) {
   const int ny = (a.D + kBlockRows<X> - 1) / kBlockRows<X>;
-  if ((int64_t)(a.N / 8) * ny <= 256) launch_rows<T, X, EPI, S, 1, NV>(a, s);
-  else if ((int64_t)(a.N / 16) * ny <= 256) launch_rows<T, X, EPI, S, 2, NV>(a, s);
-  else launch_rows<T, X, EPI, S, 4, NV>(a, s);
+  if ((int64_t)(a.N / 16) * ny > 256) launch_rows<T, X, EPI, S, 4, NV>(a, s);
+  else if ((int64_t)(a.N / 8) * ny > 256) launch_rows<T, X, EPI, S, 2, NV>(a, s);
+  else launch_rows<T, X, EPI, S, 1, NV>(a, s);
 }
 
 // ---------------------------------------------------------------------------
