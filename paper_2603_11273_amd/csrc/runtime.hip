@@ -794,14 +794,20 @@ asr_status cross_kv(asr_ctx* c, const void* E, int n, int slot0) {
 // ---------------------------------------------------------------------------
 // Decode pipeline (the rows' slots, tokens and positions already in d_rows)
 // ---------------------------------------------------------------------------
+// Rows up to which every block of a product repeats the preparation of its
+// rows instead of a kernel of its own.  LayerNorms: up to eight, one for each of
+// the waves that prepare rows.  A step of 8 rows with them inside / apart, us: base
+// 274 / 292, small 583 / 623, large-v3 1779 / 1874 (one row 234 / 254, 479 / 528,
+// 1444 / 1542); two rows a wave would still gain 1 to 4 % at 9 to 16 rows (12 rows
+// of large-v3 2028 / 2080), three lose (24 rows 2776 / 2746).  The merge of the
+// cross attention's records: up to two rows, as a block reads 21 KB a row for it
+// (d = 1280).  One row inside / apart: base 234 / 242, small 479 / 490, large-v3
+// 1444 / 1460; two: 241 / 246, 509 / 514, 1493 / 1478; three: 249 / 250, 529 / 524,
+// 1582 / 1524; four: 253 / 252, 541 / 528, 1690 / 1597.
+constexpr int kNormRows = 8, kMergeRows = 2;
+
 // A decode product (rows_*), timed with the traffic it cannot do without:
 // weights, operand and result once.
-// Rows up to which every block of a product repeats the preparation of its
-// rows: eight LayerNorms go to eight waves at once (one row at d = 1280: 4.5 us
-// for the cross query's product with it, 3.5 + 3.4 us apart); merging four
-// rows' records reads 84 KB a block.
-constexpr int kNormRows = 8, kMergeRows = 4;
-
 template <typename T, class F>
 void drows(asr_ctx* c, int D, int N, int K, double xy_bytes, F&& f) {
   timed(c, ASR_K_DGEMM, 2.0 * D * N * K, (double)N * K * c->es + xy_bytes, f);
