@@ -9,10 +9,11 @@
 //    O^T = V^T P^T product directly as its B operand, and the per-query
 //    rescale is a per-lane multiply.  Softmax runs in fp32 with exp2.
 //  * flash_attn_f32: the same result in fp32 MFMA, keys split over a block's waves.
-//  * decode self / cross attention: one block per (row, head), streaming the
-//    row's cache once: scores for all keys, exact softmax, then the
-//    probability-weighted value sum.  The self variant first stores this
-//    step's key and value at the slot's position.
+//  * decode self attention: one block per (row, head) over the row's cached keys
+//    in parts joined by an online softmax; this step's key and value go into
+//    the cache at the slot's position.
+//  * decode cross attention: one block per (row, head, chunk of the 1500 keys),
+//    each leaving a record (max, sum, weighted values) that is merged later.
 #include "asr_device.h"
 
 #include <algorithm>
@@ -28,8 +29,8 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 u) {
 // ---------------------------------------------------------------------------
 // Encoder flash attention (bf16)
 //
-// Block = NW (8 or 4) waves x 32 queries of one (clip, head); tiles of 64 keys.  K
-// comes from the fused QKV buffer, V from the per-head transposed copy the
+// Block = NW (8 or 4) waves x 32 queries of one (clip, head); tiles of 64 keys.
+// K comes from the fused QKV buffer, V from the per-head transposed copy the
 // QKV GEMM writes (V^T[dim][position], zero past 1500).  S^T = K Q^T is
 // computed per 32-key x 32-query block, so in the MFMA output layout a lane
 // owns one query: the row max needs one cross-lane exchange (lane ^ 32) and
@@ -112,8 +113,9 @@ void k_flash_bf16(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ vt,
 
   // Direct loads: wave w fills rows 8w .. 8w+7 of both tiles (and, of four waves,
   // rows 32 + 8w .. as well); lane l lands 16 bytes at slot l % 8 of row 8w + l / 8
-  // and fetches the chunk that the swizzle (the same 32 rows on) puts there.  K rows past position 1499 re-read row 1499 (their
-  // scores are masked); V^T rows are padded to kVtLd >= 64 NT positions.
+  // and fetches the chunk that the swizzle (the same 32 rows on) puts there.  K
+  // rows past position 1499 re-read row 1499 (their scores are masked); V^T rows
+  // are padded to kVtLd >= 64 NT positions.
   const int lrow = wave * 8 + (lane >> 3);
   const int lch = (lane & 7) ^ ((lrow >> 1) & 7);
   const uint32_t k_lds = __builtin_amdgcn_readfirstlane(
@@ -147,7 +149,6 @@ void k_flash_bf16(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ vt,
   f32x16 zero16;
 #pragma unroll
   for (int r = 0; r < 16; ++r) zero16[r] = 0.f;
-  // all eight K fragments in flight before the first MFMA needs one
   // scores of tile t: four K fragments in flight per 32-key block
   auto scores = [&](int t, f32x16 (&s)[2]) {
     const bf16_t* Kc = Ks[t % S];

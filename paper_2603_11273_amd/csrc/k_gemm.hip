@@ -6,7 +6,7 @@
 //    all decoder layers' cross K/V into a slot's cache).
 //  * gemm_f32: the same contract on fp32 MFMA (the fp32 model path).
 //  * vocab_argmax_bf16: the tied vocabulary projection fused with a per-row
-//    argmax (lowest index on ties) over each 64-column tile, finished by a
+//    argmax (lowest index on ties) over each 32-row tile of the table, finished by a
 //    deterministic cross-tile reduction.
 #include "asr_device.h"
 
@@ -1372,7 +1372,7 @@ static bool direct_epi_ok(const Epilogue& e, int M, int N) {
   if (N % 8 != 0 || ((uintptr_t)e.out & 15) != 0) return false;
   if (e.kind == EPI_XKV) return e.d_model % 64 == 0 && e.slot_stride % 8 == 0;
   if (e.kind == EPI_QKV) {
-    // tiles of 256 columns never mix q / k with V; V^T fits a buffer resource
+    // tiles of up to 256 columns never mix q / k with V; V^T fits a buffer resource
     const int64_t vt_bytes = (int64_t)((M + kCtx - 1) / kCtx) * e.n_head * kHeadDim * kVtLd * 2;
     if (e.d_model % 128 != 0 || N != 3 * e.d_model || ((uintptr_t)e.out2 & 7) != 0 ||
         vt_bytes >= (int64_t)INT32_MAX)
