@@ -65,14 +65,6 @@ struct Epilogue {
   void* out2;           // QKV: transposed V [B][H][64][kVtLd]
 };
 
-// Element offset in a slot's cross cache ([layer][K, V][head][1500][64]), at
-// position 0, of column n of the cross K/V product (2 d columns a layer, K then
-// V, 64 a head: n / 64 counts them all).  The columns up to the next multiple of
-// 64 follow this one.
-__host__ __device__ constexpr int64_t xkv_col(int n) {
-  return (int64_t)(n / kHeadDim) * kCtx * kHeadDim + n % kHeadDim;
-}
-
 // Dense GEMM C[M][N] = A[M][K] . W[N][K]^T with a fused epilogue.
 void gemm_bf16(const AView& a, const bf16_t* w, int M, int N, int K, const Epilogue& e,
                hipStream_t s);
