@@ -47,11 +47,13 @@ __device__ __forceinline__ int rl_swz(int row) { return (row >> 1) & 7; }
 // would wait for the weights too).  The products are v_mfma_f32_32x32x16_bf16 /
 // v_mfma_f32_32x32x2_f32 with the weight rows as first operand (repeated when
 // there are fewer than 32); the slices meet in LDS.
-// Measured at d = 1280 in a graph-replayed step, before and after, one row (the
-// launch's fixed part is near 3 us): QKV 6.9 us as partial sums + 4.3 for the
-// residual LayerNorm before it, now 6.2 with it; FC1 11.5 + 4.3, now 7.6; FC2
-// 7.2; out-projection 3.5.  128 rows: QKV 8.5, now 8.9 (nothing left for the
-// attention to add up); FC1 12.3, 12.3; out-projection 6.5 + 4.8, now 5.6 + 4.7.
+// Measured at d = 1280 in the kernel trace of a graph-replayed step (us), as split-K
+// partial sums, which a kernel of residual and LayerNorm (4.2 for one row, 4.8 for
+// 128) or the attention added up, and now.  One row (the launch's fixed part is
+// near 3): QKV 7.4, now 5.5 with its LayerNorm; out-projection 4.2, now 3.7; cross
+// query 3.6, now 4.4 with its LayerNorm; FC1 11.7, now 7.2 with its LayerNorm; FC2
+// 9.3, now 7.1.  128 rows: QKV 8.4, now 8.7; out-projection 5.2, 5.5; cross query
+// 5.8, 5.2; FC1 12.1, 11.9; the LayerNorms apart 4.7 each.
 template <typename T, int X, int EPI, int S, int WR8, int NV>
 __global__ __launch_bounds__((S + (X == RX_MEM ? 0 : RL_LW)) * 64) void k_rows(RowsArgs a) {
   constexpr int ES = sizeof(T), WR = 8 * WR8;
@@ -232,7 +234,8 @@ static void launch_rows_any(const RowsArgs& a, hipStream_t s) {
 // waves: the weights, which come cold from HBM, NW - 1 chunks ahead, x, an L2
 // hit, NX - 1 ahead.  The time is that of a chain of chunks (load, barrier,
 // read, MFMA), so two blocks a CU and short chains: N = 1280, K = 5120, 128 rows
-// 11.7 us in 8 parts with 72 KB of LDS, 14.1 in 4 parts with 152 KB.
+// 11.7 us in 8 parts with 72 KB of LDS, 14.1 in 4 parts with 152 KB (9.9 in 5 parts
+// that added their chunks in another order, so not the sums of a row alone).
 // ---------------------------------------------------------------------------
 struct WideArgs {
   const bf16_t* x;      // [D][K]
